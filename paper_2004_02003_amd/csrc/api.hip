@@ -92,6 +92,8 @@ struct bto_ctx {
     PState* bpos[2] = {nullptr, nullptr};
     uint32_t* bid[2] = {nullptr, nullptr};
     int tb = 0;                   // bucket buffer of the current step
+    int tile_live_slot = 0;       // count slot that holds the live particles of the tile layout
+    int32_t tile_step0 = 0;       // steps done when the tile layout was entered
     std::string err;
 };
 
@@ -158,6 +160,12 @@ int bto_create(const bto_block* blk, int64_t max_particles, int32_t device, bto_
     }
     c->geom.sy = (uint32_t)blk->n[0];
     c->geom.sz = (uint32_t)blk->n[0] * (uint32_t)blk->n[1];
+    {
+        const uint32_t npts = c->geom.sz * (uint32_t)blk->n[2];  // at most 2^30
+        c->geom.sy3 = 3u * c->geom.sy;
+        c->geom.sz3 = 3u * c->geom.sz;
+        c->geom.last_odd = (npts & 1u) ? 3u * (npts - 2u) : 0xFFFFFFFFu;
+    }
     if (hipSetDevice(device) != hipSuccess) {
         delete c;
         return BTO_EINVAL;
@@ -345,15 +353,16 @@ static int tile_setup(bto_ctx* c, int dtype, hipStream_t s) {
     std::sort(mt.begin(), mt.end());
     const size_t longest = ((size_t)ntiles + NSEG - 1) / NSEG;
     const int grid = (int)(longest * NSEG);
-    std::vector<int32_t> order((size_t)grid, -1);
+    std::vector<int32_t> order((size_t)grid, -1), slot_of((size_t)ntiles, -1);
     for (int x = 0; x < NSEG; ++x) {
         const size_t b = (size_t)ntiles * x / NSEG, e = (size_t)ntiles * (x + 1) / NSEG;
-        for (size_t k = b; k < e; ++k) order[(k - b) * NSEG + x] = mt[k].second;
+        for (size_t k = b; k < e; ++k) {
+            const int32_t t = mt[k].second, tx = t % tg.nt[0], ty = t / tg.nt[0] % tg.nt[1], tz = t / (tg.nt[0] * tg.nt[1]);
+            const size_t w = (k - b) * NSEG + x;
+            order[w] = tx | ty << 10 | tz << 20;
+            slot_of[(size_t)t] = (int32_t)w;  // bucket w holds the tile of workgroup w, so there are `grid` buckets
+        }
     }
-    // bucket b holds the tile of workgroup b, so there are `grid` buckets
-    std::vector<int32_t> slot_of((size_t)ntiles, -1);
-    for (int b = 0; b < grid; ++b)
-        if (order[(size_t)b] >= 0) slot_of[(size_t)order[(size_t)b]] = b;
     const size_t o_bytes = ((size_t)grid * sizeof(int32_t) + 255) & ~(size_t)255;
     const size_t s_bytes = ((size_t)ntiles * sizeof(int32_t) + 255) & ~(size_t)255;
     const size_t c_bytes = ((3 * (size_t)grid + 3) * sizeof(uint32_t) + 255) & ~(size_t)255;
@@ -422,6 +431,8 @@ static int tile_enter(bto_ctx* c, int dtype, int max_seg_blocks, hipStream_t s) 
     e = launch_tile_bin(a, max_seg_blocks, s);
     if (e != hipSuccess) return hip_fail(c, e, "tile bin launch");
     c->tile_layout = true;
+    c->tile_live_slot = c->slot;
+    c->tile_step0 = c->steps_done;
     return BTO_OK;
 }
 
@@ -452,8 +463,9 @@ static int tile_live(bto_ctx* c, double* out_end, uint8_t* out_flag, int32_t* ou
     return e == hipSuccess ? BTO_OK : hip_fail(c, e, "tile live launch");
 }
 
-// One RK4 step of every live particle in the tile layout: the tile launch,
-// then the list launch; the rings advance by one.
+// One RK4 step of every live particle in the tile layout (gathering: one
+// launch; staged: the tile launch, then the list launch); the rings advance by
+// one.
 static int tile_step(bto_ctx* c, const void* f0, const void* f1, double h, int dtype, int mode, int rec,
                      hipStream_t s) {
     const int sl = c->slot, sl1 = (c->slot + 1) % 3, sl2 = (c->slot + 2) % 3;
@@ -461,6 +473,7 @@ static int tile_step(bto_ctx* c, const void* f0, const void* f1, double h, int d
     a.f0 = static_cast<const char*>(f0);
     a.f1 = static_cast<const char*>(f1);
     a.h = h;
+    a.hs = step_sizes(c->geom, h);
     a.g = c->geom;
     a.tg = c->tg;
     a.step0 = c->steps_done;
@@ -486,19 +499,26 @@ static int tile_step(bto_ctx* c, const void* f0, const void* f1, double h, int d
     a.rec_meta = c->rec_meta;
     a.rec_out = c->rec_out;
     a.psteps = c->psteps;
-    a.live_out = c->counts + NSEG * CSTRIDE * sl1;
-    a.live_clear = c->counts + NSEG * CSTRIDE * sl2;
-    hipError_t e = launch_tile_step(a, dtype, mode, rec, c->tiles == 1 ? 1 : 0, s);
-    if (e != hipSuccess) return hip_fail(c, e, "tile step launch");
-    TileListArgs l{};
-    l.s = a;
-    l.in_pos = c->pos[c->cur];
-    l.in_id = c->id[c->cur];
-    l.in_count = c->lcount + sl;
+    a.live = c->counts + NSEG * CSTRIDE * c->tile_live_slot;
+    a.backwards = c->steps_done & 1;
+    a.attempts = (uint32_t)(c->steps_done - c->tile_step0 + 1);
     int64_t lg = c->n_seeds / (BLOCK * 32);
     lg = lg < 64 ? 64 : (lg > 1024 ? 1024 : lg);
-    e = launch_tile_list(l, dtype, mode, rec, (int)lg, s);
-    if (e != hipSuccess) return hip_fail(c, e, "tile list launch");
+    hipError_t e;
+    if (c->tiles == 1) {
+        e = launch_tile_stage(a, dtype, mode, rec, s);
+        if (e != hipSuccess) return hip_fail(c, e, "tile step launch");
+        TileListArgs l{};
+        l.s = a;
+        l.in_pos = c->pos[c->cur];
+        l.in_id = c->id[c->cur];
+        l.in_count = c->lcount + sl;
+        e = launch_tile_list(l, dtype, mode, rec, (int)lg, s);
+        if (e != hipSuccess) return hip_fail(c, e, "tile list launch");
+    } else {
+        e = launch_tile_step(a, dtype, mode, rec, (int)lg, s);
+        if (e != hipSuccess) return hip_fail(c, e, "tile step launch");
+    }
     c->slot = sl1;
     c->cur = 1 - c->cur;
     c->tb = 1 - c->tb;
@@ -678,7 +698,9 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
     if (dtype < BTO_F32 || dtype > BTO_BF16) return fail(c, BTO_EINVAL, "unknown dtype %d", dtype);
     const int tmode = flags & ~(BTO_RECORD_EXIT | BTO_RECORD_CKPT | BTO_SAMPLE_FP64);
     if (tmode != BTO_TIME_LINEAR && tmode != BTO_TIME_FROZEN) return fail(c, BTO_EINVAL, "unknown flags %d", flags);
-    const int mode = tmode | ((flags & BTO_SAMPLE_FP64) ? MODE_FP64 : 0);
+    // byte offsets into a grid of at most 4 GiB fit 32 bits
+    const uint64_t grid_bytes = 3ull * c->geom.sz * (uint64_t)c->geom.n[2] * (dtype == BTO_F32 ? 4u : 2u);
+    const int mode = tmode | ((flags & BTO_SAMPLE_FP64) ? MODE_FP64 : 0) | (grid_bytes > (1ull << 32) ? MODE_WIDE : 0);
     const int rec = (flags & BTO_RECORD_EXIT) ? 1 : 0;
     const bool rec_ck = (flags & BTO_RECORD_CKPT) != 0;
     for (int32_t q = 0; q <= n_steps; ++q)
@@ -728,7 +750,7 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
         return BTO_OK;
     }
     const int lpp = dtype == BTO_F32 ? c->lanes_per_particle : 1;
-    int per_cu = advect_max_blocks_per_cu(dtype, mode, lpp, rec);
+    int per_cu = advect_max_blocks_per_cu(dtype, mode & ~MODE_WIDE, lpp, rec);
     if (c->blocks_per_cu_cap > 0 && c->blocks_per_cu_cap < per_cu) per_cu = c->blocks_per_cu_cap;
     const int R = blocks_per_seg(c, max_seg * lpp, per_cu);
     // launches of (nearly) equal length, at most steps_per_launch steps each
@@ -776,7 +798,7 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
         a.rec_meta = c->rec_meta;
         a.rec_out = c->rec_out;
         a.psteps = c->psteps;
-        hipError_t e = launch_advect(a, dtype, mode, lpp, rec, R, s);
+        hipError_t e = launch_advect(a, dtype, mode & ~MODE_WIDE, lpp, rec, R, s);
         if (e != hipSuccess) return hip_fail(c, e, "advect launch");
         c->cur = 1 - c->cur;
         c->slot = (c->slot + 1) % 3;
@@ -929,14 +951,17 @@ int bto_stats(bto_ctx* c, bto_stats_t* out, void* stream) {
     hipStream_t s = (hipStream_t)stream;
     uint32_t cnt[NSEG * CSTRIDE];
     unsigned long long psv[NSEG * PSTRIDE];
-    hipError_t e = hipMemcpyAsync(cnt, c->counts + NSEG * CSTRIDE * c->slot, sizeof cnt, hipMemcpyDeviceToHost, s);
+    const int slot = c->tile_layout ? c->tile_live_slot : c->slot;
+    hipError_t e = hipMemcpyAsync(cnt, c->counts + NSEG * CSTRIDE * slot, sizeof cnt, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipMemcpyAsync(psv, c->psteps, sizeof psv, hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(c, e, "stats readback");
-    int64_t live = 0;
+    uint32_t live = 0;  // below 2^32; the tile layout's counters are modulo 2^32 each
     for (int x = 0; x < NSEG; ++x) live += cnt[x * CSTRIDE];
     unsigned long long ps = 0;
     for (int x = 0; x < NSEG; ++x) ps += psv[x * PSTRIDE];
+    // the tile steps count the attempts of the particles that ended; the live ones attempted every step
+    if (c->tile_layout) ps += (unsigned long long)live * (unsigned long long)(c->steps_done - c->tile_step0);
     out->n_live = live;
     out->particle_steps = (int64_t)ps;
     return BTO_OK;

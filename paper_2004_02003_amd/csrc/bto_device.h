@@ -41,6 +41,12 @@ enum : int { MODE_LINEAR = 0, MODE_FROZEN = 1 };
 // velocities in FP64; trilinear weights applied in FP32 to the corner
 // differences from the cell's base corner (trilerp / trilerp_mid for double).
 constexpr int MODE_FP64 = 2;
+// Mode bit of the gathering kernels: the grids exceed 4 GiB, byte offsets are
+// 64-bit.  Smaller grids take a scalar base and a 32-bit offset per load (no
+// 64-bit address arithmetic, one address register instead of two).
+constexpr int MODE_WIDE = 4;
+template <int MODE>
+constexpr bool is_wide = (MODE & MODE_WIDE) != 0;
 template <int MODE>
 constexpr bool is_frozen = (MODE & MODE_FROZEN) != 0;
 // Arithmetic type of the sampler in a mode.
@@ -93,6 +99,9 @@ struct Geom {
     double nmax[3];      // n - 1: the closed box is [0, nmax]
     double inv_sp[3];    // 1 / spacing: world velocity -> cells per unit time
     uint32_t sy, sz;     // point strides of y and z (n <= 1024 per axis)
+    uint32_t sy3, sz3;   // the same strides in values (3 per point)
+    uint32_t last_odd;   // grids of an odd number of points: the first value of the grid's last two
+                         // points, whose 16-bit window starts 2 bytes early; else none
 };
 
 __device__ __forceinline__ bool inside(const Geom& g, const double p[3]) {
@@ -124,6 +133,35 @@ __device__ __forceinline__ CellR<R> locate(const Geom& g, const double p[3]) {
     return c;
 }
 
+// The same for the gathering step, whose points may lie outside the block
+// once a particle's step has ended: the conversion truncates (the floor of an
+// inside point, whose coordinates are not negative), saturates and maps NaN
+// to 0, and the index is clamped on both sides, so the cell is always one of
+// the block's.
+template <class R>
+struct GatherCell {
+    uint32_t val;  // value index (3 per point) of corner (i, j, k): below 3 * 2^30
+    R f[3];
+};
+
+template <class R = float>
+__device__ __forceinline__ GatherCell<R> locate_clamped(const Geom& g, const double p[3]) {
+    GatherCell<R> c;
+    uint32_t i[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        int v;
+        asm("v_cvt_i32_f64 %0, %1" : "=v"(v) : "v"(p[d]));  // in C an out-of-range conversion is undefined
+        v = v < 0 ? 0 : v;
+        v = v > g.n[d] - 2 ? g.n[d] - 2 : v;
+        i[d] = (uint32_t)v;
+        c.f[d] = (R)(p[d] - (double)v);
+    }
+    // strides of at most 3 * 2^20 and indices below 2^10: the 24-bit products are exact
+    c.val = 3u * i[0] + __umul24(g.sy3, i[1]) + __umul24(g.sz3, i[2]);
+    return c;
+}
+
 __device__ __forceinline__ float lerp(float a, float b, float t) { return fmaf(t, b - a, a); }
 __device__ __forceinline__ float fmar(float a, float b, float c) { return fmaf(a, b, c); }
 __device__ __forceinline__ double fmar(double a, double b, double c) { return fma(a, b, c); }
@@ -139,15 +177,18 @@ constexpr uint32_t NO_CELL = 0xFFFFFFFFu;
 
 struct __attribute__((packed, aligned(4))) Row32 { float v[6]; };
 
+typedef _Float16 Half2 __attribute__((ext_vector_type(2)));
+
 // Value (r, q) of a row of two 16-bit points packed as three dwords
-// (x0|y0, z0|x1, y1|z1), converted to FP32 (exact).
+// (x0|y0, z0|x1, y1|z1), converted to FP32 (exact).  An f16 half is taken as a
+// vector element, which the compiler folds into the FMA that uses it
+// (v_fma_mix_f32) instead of converting it first.
 template <int DT>
 __device__ __forceinline__ float dec16(uint32_t w, int hi) {
-    const uint32_t h = hi ? (w >> 16) : (w & 0xFFFFu);
     if constexpr (DT == DT_F16) {
-        return (float)__builtin_bit_cast(_Float16, (uint16_t)h);
+        return (float)__builtin_bit_cast(Half2, w)[hi];
     } else {
-        return __uint_as_float(h << 16);
+        return __uint_as_float(hi ? w & 0xFFFF0000u : w << 16);
     }
 }
 
@@ -213,6 +254,112 @@ __device__ __forceinline__ void ensure(const Geom& g, const char* V, uint32_t ba
         c.base = base;
     }
 }
+
+// ---------------------------------------------------------------------------
+// Corner values of one cell for the gathering step (rk4_step_gather).  The
+// registers hold what the loads returned and nothing is done to it until the
+// sampler reads it, so a cell's loads -- and those of a second level issued
+// after them -- are all in flight before the first wait.  (CellCache shifts a
+// 16-bit row into place right behind its load, which makes the two levels of
+// a midpoint stage two round trips.)
+//   FP32    the rows' 6 values;
+//   16 bit  per row the 16-byte window that holds its 12 bytes, starting on
+//           a dword.  Rows 0 to 2 start at the dword of their first byte; row
+//           3 may be the last of the grid, so its window ends with the row's
+//           last dword instead and begins 2 or 4 bytes before the row (2-byte
+//           aligned in the one case of the last row of a grid of an odd number
+//           of points).  No window leaves the grid.
+// A cell is known by its first value's index.  Byte offsets from the grid's
+// start are 32-bit, 64-bit (WIDE) for grids beyond 4 GiB.
+// ---------------------------------------------------------------------------
+template <bool WIDE>
+__device__ __forceinline__ const char* bytes_at(const char* V, uint32_t unit, int shift) {
+    return WIDE ? V + ((uint64_t)unit << shift) : V + (unit << shift);
+}
+
+// A register value whose origin the compiler cannot see (no instruction).
+__device__ __forceinline__ uint32_t opaque(uint32_t v) {
+    asm("" : "+v"(v));
+    return v;
+}
+
+// The rows of a cell as the sampler reads them.
+template <int DT>
+struct Rows16 {
+    uint32_t W[4][3];
+    __device__ __forceinline__ float v(int r, int q) const { return dec16<DT>(W[r][q >> 1], q & 1); }
+};
+
+template <int DT>
+struct GatherCache {
+    uint32_t val;      // first value of the cell (NO_CELL: none)
+    uint32_t W[4][4];
+    uint32_t sel3;     // byte selector of row 3 in its window
+    template <bool WIDE>
+    __device__ __forceinline__ void load(const Geom& g, const char* V, uint32_t b) {
+        const uint32_t b3 = b + (g.sy3 + g.sz3);
+        const bool early = b3 == g.last_odd;
+        const char* p[4];
+        if constexpr (WIDE) {
+            p[0] = bytes_at<true>(V, b >> 1, 2);
+            p[1] = bytes_at<true>(V, (b + g.sy3) >> 1, 2);
+            p[2] = bytes_at<true>(V, (b + g.sz3) >> 1, 2);
+            p[3] = bytes_at<true>(V, (b3 - 1u) >> 1, 2) - (early ? 2 : 0);
+        } else {
+            const uint32_t o = 2u * b;
+            p[0] = V + (o & ~3u);
+            p[1] = V + ((o + 2u * g.sy3) & ~3u);
+            p[2] = V + ((o + 2u * g.sz3) & ~3u);
+            p[3] = V + (((o + 2u * (g.sy3 + g.sz3) - 2u) & ~3u) - (early ? 2u : 0u));
+        }
+        val = b;
+        sel3 = (b3 & 1u) && !early ? 0x05040302u : 0x07060504u;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const uint4 q = *reinterpret_cast<const uint4*>(p[r]);
+            W[r][0] = q.x;
+            W[r][1] = q.y;
+            W[r][2] = q.z;
+            W[r][3] = q.w;
+        }
+    }
+    __device__ __forceinline__ Rows16<DT> rows(const Geom& g) const {
+        // The shift and the selector are made opaque: otherwise the compiler
+        // sees that a cell kept from one stage to the next decodes to the same
+        // values, and holds all of them in registers to save the decoding.
+        Rows16<DT> o;
+        const uint32_t b = opaque(val), sel = opaque(sel3);
+        const uint32_t par[3] = {0u, g.sy3, g.sz3};  // odd strides change a row's alignment
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const uint32_t sh = (b ^ par[r]) << 4;  // the instruction takes 5 bits: 0 or 16
+#pragma unroll
+            for (int j = 0; j < 3; ++j) o.W[r][j] = __builtin_amdgcn_alignbit(W[r][j + 1], W[r][j], sh);
+        }
+#pragma unroll
+        for (int j = 0; j < 3; ++j) o.W[3][j] = __builtin_amdgcn_perm(W[3][j + 1], W[3][j], sel);
+        return o;
+    }
+};
+
+template <>
+struct GatherCache<DT_F32> {
+    uint32_t val;
+    float R[4][6];
+    __device__ __forceinline__ float v(int r, int q) const { return R[r][q]; }
+    template <bool WIDE>
+    __device__ __forceinline__ void load(const Geom& g, const char* V, uint32_t b) {
+        const uint32_t step[4] = {0u, g.sy3, g.sz3, g.sy3 + g.sz3};
+        val = b;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const Row32 x = *reinterpret_cast<const Row32*>(bytes_at<WIDE>(V, b + step[r], 2));
+#pragma unroll
+            for (int q = 0; q < 6; ++q) R[r][q] = x.v[q];
+        }
+    }
+    __device__ __forceinline__ const GatherCache& rows(const Geom&) const { return *this; }
+};
 
 // Trilinear corner weights w[r][x] (row r as above, x-offset x), times `scale`.
 template <class R>
@@ -487,6 +634,17 @@ __device__ __forceinline__ bool fetch(const Geom&, const char*, const C& c, LdsC
     return true;
 }
 
+// Mark a cache as holding no cell.
+template <class Cache>
+__device__ __forceinline__ void forget(Cache& k) {
+    k.base = NO_CELL;
+}
+
+template <int DT>
+__device__ __forceinline__ void forget(GatherCache<DT>& k) {
+    k.val = NO_CELL;
+}
+
 template <class R>
 __device__ __forceinline__ bool finite3(const R k[3]) {
     return __builtin_isfinite(k[0]) && __builtin_isfinite(k[1]) && __builtin_isfinite(k[2]);
@@ -619,6 +777,139 @@ __device__ __forceinline__ int rk4_step(const Geom& g, const char* V0, const cha
     x[1] = y[1];
     x[2] = y[2];
     return S_VALID;
+}
+
+// Wait for every load issued so far.
+__device__ __forceinline__ void wait_loads() {
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Step sizes in cells per axis: h / spacing, half and a sixth of it.
+struct StepSizes {
+    double full[3], half[3], sixth[3];
+};
+
+__host__ __device__ __forceinline__ StepSizes step_sizes(const Geom& g, double h) {
+    StepSizes s;
+    for (int d = 0; d < 3; ++d) {
+        s.full[d] = h * g.inv_sp[d];
+        s.half[d] = 0.5 * s.full[d];
+        s.sixth[d] = s.full[d] * (1.0 / 6.0);
+    }
+    return s;
+}
+
+// inside() without short cuts: six compares and their masks cost less than a
+// branch each.
+__device__ __forceinline__ bool inside_flat(const Geom& g, const double p[3]) {
+    return (p[0] >= 0.0) & (p[0] <= g.nmax[0]) & (p[1] >= 0.0) & (p[1] <= g.nmax[1]) & (p[2] >= 0.0) &
+           (p[2] <= g.nmax[2]);
+}
+
+// The same step for the gathering kernels, arranged for few dependent round
+// trips to memory and few instructions: the same arithmetic in the same order
+// on the same corner values, so the result is bit-identical to rk4_step's.
+//   * Both levels of a midpoint stage load together; level n + 1 is never in
+//     the cache when a step begins, and at the third stage both levels hold
+//     the second stage's cell, so one test serves both: four round trips
+//     instead of six.
+//   * A lane whose step has ended stays in the wavefront's flow: its remaining
+//     stages sample some cell of the block and change nothing, which costs
+//     less than a branch and a saved execution mask per event.
+//   * A velocity that is not finite gives a point that is not inside, so the
+//     one test finds both events; which of the two it was is looked up behind
+//     it.
+//   * Step sizes in scalar registers, 32-bit offsets from a scalar base, the
+//     conversions of f16 values folded into the FMAs (tile_gather_kernel, f16:
+//     1,411 vector instructions and 127 registers before, 982 and 91 now).
+// On entry A holds a cell of level n (or NO_CELL), B nothing; x is inside.
+// one_by_one (uniform): wait for level n before level n + 1 is asked for, as
+// rk4_step does -- two round trips, but half the lines in flight, which is the
+// better where the wavefronts' lines no longer fit the L1 (see the callers).
+template <int DT, int MODE, class OnExit>
+__device__ __forceinline__ int rk4_step_gather(const Geom& g, const char* V0, const char* V1, const StepSizes& hs,
+                                               double* x, GatherCache<DT>& A, GatherCache<DT>& B, bool one_by_one,
+                                               OnExit&& on_exit) {
+    using R = SampleT<MODE>;
+    constexpr bool W = is_wide<MODE>;
+    int status = S_VALID;
+    R k[3], k1[3], k23[3];
+    double y[3];
+    // after a stage: y = x + hq v and the event tests
+    const auto point = [&](const double* hq, const R* v) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) y[d] = fma(hq[d], (double)v[d], x[d]);
+        if ((status == S_VALID) & !inside_flat(g, y)) {
+            if (finite3(k)) {
+                on_exit(y);
+                status = S_TERMINATED;
+            } else {
+                status = S_INVALID;
+            }
+        }
+    };
+
+    // b: the cell without what the tests below say about it (where a test says
+    // that a cell is the cached one, the compiler would compute the addresses
+    // of the other level once from each)
+    GatherCell<R> c = locate_clamped<R>(g, x);
+    uint32_t b = opaque(c.val);
+    if (A.val != c.val) A.template load<W>(g, V0, b);
+    trilerp(A.rows(g), c.f, k);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) k1[d] = k[d];
+    point(hs.half, k);
+
+    c = locate_clamped<R>(g, y);
+    b = opaque(c.val);
+    if (A.val != c.val) A.template load<W>(g, V0, b);
+    if constexpr (!is_frozen<MODE>) {
+        if (one_by_one) wait_loads();
+        B.template load<W>(g, V1, b);
+        trilerp_mid(A.rows(g), B.rows(g), c.f, k);
+    } else {
+        trilerp(A.rows(g), c.f, k);
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) k23[d] = k[d];
+    point(hs.half, k);
+
+    c = locate_clamped<R>(g, y);
+    b = opaque(c.val);
+    if (A.val != c.val) {
+        A.template load<W>(g, V0, b);
+        if constexpr (!is_frozen<MODE>) {
+            if (one_by_one) wait_loads();
+            B.template load<W>(g, V1, b);
+        }
+    }
+    if constexpr (!is_frozen<MODE>) {
+        trilerp_mid(A.rows(g), B.rows(g), c.f, k);
+    } else {
+        trilerp(A.rows(g), c.f, k);
+    }
+#pragma unroll
+    for (int d = 0; d < 3; ++d) k23[d] = k23[d] + k[d];
+    point(hs.full, k);
+
+    c = locate_clamped<R>(g, y);
+    b = opaque(c.val);
+    if constexpr (!is_frozen<MODE>) {
+        if (B.val != c.val) B.template load<W>(g, V1, b);
+        trilerp(B.rows(g), c.f, k);
+    } else {
+        if (A.val != c.val) A.template load<W>(g, V0, b);
+        trilerp(A.rows(g), c.f, k);
+    }
+    R ks[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) ks[d] = (k1[d] + k[d]) + (R)2 * k23[d];
+    point(hs.sixth, ks);
+#pragma unroll
+    for (int d = 0; d < 3; ++d) x[d] = status == S_VALID ? y[d] : x[d];
+    return status;
 }
 
 // Stepping with two cache slots whose roles alternate: step s reads level n

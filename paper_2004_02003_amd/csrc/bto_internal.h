@@ -33,6 +33,17 @@ __device__ __forceinline__ T* in_global(T* p) {
     return (T*)(G)(uintptr_t)p;
 }
 
+// A value that is the same in every lane, moved to scalar registers (in
+// assembly: the compiler drops its own builtin where it knows the value to be
+// uniform, and keeps it in vector registers all the same).
+__device__ __forceinline__ double uniform(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    uint32_t lo, hi;
+    asm("v_readfirstlane_b32 %0, %1" : "=s"(lo) : "v"((uint32_t)b));
+    asm("v_readfirstlane_b32 %0, %1" : "=s"(hi) : "v"((uint32_t)(b >> 32)));
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 struct Segs {
     int64_t base[NSEG];  // first slot of each segment
 };
@@ -233,27 +244,29 @@ struct TileStepArgs {
     const char* f0;           // grid of cycle n
     const char* f1;           // grid of cycle n + 1
     double h;
+    StepSizes hs;             // of h, for the gathering kernels
     Geom g;
     TileGeom tg;
     int32_t step0;            // index of this step in the interval
-    const int32_t* order;     // tile of bucket b = workgroup b (-1: none); b = k * NSEG + x is the
-                              // k-th tile of XCD x's run
+    const int32_t* order;     // tile coordinates (10 bits each) of bucket b = workgroup b (-1: none);
+                              // b = k * NSEG + x is the k-th tile of XCD x's run
     int32_t order_len;        // buckets (a multiple of NSEG)
     const uint32_t* tc_in;    // this step's bucket counts
     uint32_t* tc_clear;       // bucket counts cleared for the step after next
     const PState* in_pos;     // this step's buckets
     const uint32_t* in_id;
     TileOut out;
-    PState* list_pos;         // this step's list (deferred particles appended)
+    PState* list_pos;         // this step's list (the staged step appends deferred particles)
     uint32_t* list_id;
     uint32_t* list_count;
     uint32_t* list_clear;     // list count cleared for the step after next
     PState* rec_pos;
     int32_t* rec_meta;
     float4* rec_out;
-    unsigned long long* psteps;
-    uint32_t* live_out;       // NSEG survivor counts of the next step
-    uint32_t* live_clear;     // NSEG counts cleared for the step after next
+    unsigned long long* psteps;  // NSEG counters: attempts of the particles that ended
+    uint32_t* live;           // NSEG counters, modulo 2^32: their sum is the live particles
+    int32_t backwards;        // run each XCD's tiles in reverse order
+    uint32_t attempts;        // steps attempted in this layout by a particle ending in this step
 };
 
 struct TileListArgs {
@@ -290,9 +303,11 @@ struct TileLiveArgs {
     double* ckpt;             // checkpoint slot base: [seed id][xyz] (cell units)
 };
 
-// One workgroup per order entry; stage = 1: sample LDS-staged tiles, 0: gather
-// from the grids.
-hipError_t launch_tile_step(const TileStepArgs& a, int dtype, int mode, int rec, int stage, hipStream_t s);
+// One workgroup per order entry, gathering from the grids, and list_blocks for
+// the list; or one per order entry sampling LDS-staged tiles, the list then by
+// launch_tile_list.  mode: MODE_WIDE set for grids beyond 4 GiB.
+hipError_t launch_tile_step(const TileStepArgs& a, int dtype, int mode, int rec, int list_blocks, hipStream_t s);
+hipError_t launch_tile_stage(const TileStepArgs& a, int dtype, int mode, int rec, hipStream_t s);
 hipError_t launch_tile_list(const TileListArgs& a, int dtype, int mode, int rec, int grid, hipStream_t s);
 hipError_t launch_tile_bin(const TileBinArgs& a, int blocks_per_seg, hipStream_t s);
 hipError_t launch_tile_fill(uint32_t* p, size_t n, hipStream_t s);

@@ -4,56 +4,62 @@
 // belongs to the tile of its sampling cell); tiles run along a Hilbert curve
 // in cell space, one eighth of the curve per XCD, so neighbouring tiles run
 // close in time on one XCD and share the grid lines of their common faces in
-// its L2.  One step is two launches:
+// its L2.  A step is
 //   tile_gather_kernel  one workgroup per tile: advance every particle of the
 //   (tiles = 2)         tile one RK4 step, gathering the grid values, and
 //                       write each survivor into the bucket of the tile it
-//                       ends in (next step's buffers);
-//   tile_stage_kernel   the same with the tile's cells plus a halo of H cells
-//   (tiles = 1)         of level n (and n+1) first staged in LDS with
-//                       coalesced row loads and sampled from there; a
+//                       ends in (next step's buffers); the workgroups behind
+//                       the tiles' do the same for the list of particles that
+//                       did not fit their bucket in the previous step;
+// or two launches:
+//   tile_stage_kernel   the same for the tiles, with the tile's cells plus a
+//   (tiles = 1)         halo of H cells of level n (and n+1) first staged in
+//                       LDS with coalesced row loads and sampled from there; a
 //                       particle whose stage point needs a cell outside the
 //                       staged box is deferred: appended unchanged to this
 //                       step's list;
-//   tile_list_kernel    advance the list (deferred particles, and those that
-//                       did not fit their bucket in the previous step) with
-//                       global gathers, into the same next-step buckets.
+//   tile_list_kernel    advance the list (deferred particles and the previous
+//                       step's overflow) with global gathers, into the same
+//                       next-step buckets.
 // All sample with the same arithmetic on the same FP32 corner values, so a
 // particle's step does not depend on which kernel took it.
 //
 // Buffers (context-owned): two bucket arrays (ping-pong) of nbuckets x cap
 // slots of state + seed id, bucket b holding the tile that workgroup b runs
 // (so a workgroup loads its tile id, particle count and particles at once); a
-// ring of three bucket-count arrays (the launch pair of a step reads ring slot
-// s, appends to s+1 and clears s+2); the list
-// in the context's ping-pong particle buffers with a ring of three counts;
-// per-XCD live and particle-step counters as in the segment layout.
+// ring of three bucket-count arrays (a step reads ring slot s, appends to s+1
+// and clears s+2); the list in the context's ping-pong particle buffers with a
+// ring of three counts; per-XCD counters of the live particles and of the
+// steps attempted by particles that ended, touched only where one ended.
 #include <type_traits>
 
 #include "bto_internal.h"
 
 namespace bto {
 
-// Tile of a position's sampling cell (the cell locate() picks).
-__device__ __forceinline__ uint32_t tile_key(const Geom& g, const TileGeom& tg, const double x[3]) {
-    uint32_t t[3];
+// Tile of an inside point's sampling cell (the cell locate() picks); GATHER:
+// tiles of the gathering step, whose sides are powers of two known here.
+template <bool GATHER>
+__device__ __forceinline__ void tile_coords(const Geom& g, const TileGeom& tg, const double x[3], int t[3]) {
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        int v = (int)floor(x[d]);
+        int v = (int)x[d];
         v = v > g.n[d] - 2 ? g.n[d] - 2 : v;
-        v = v < 0 ? 0 : v;
-        t[d] = (uint32_t)v / (uint32_t)tg.T[d];
+        t[d] = GATHER ? v / TILE_GATHER[d] : v / tg.T[d];
     }
-    return t[0] + (uint32_t)tg.nt[0] * (t[1] + (uint32_t)tg.nt[1] * t[2]);
+}
+
+__device__ __forceinline__ uint32_t tile_index(const TileGeom& tg, const int t[3]) {
+    return (uint32_t)(t[0] + tg.nt[0] * (t[1] + tg.nt[1] * t[2]));
 }
 
 // Write survivors to the bucket of their tile (key: tile id): one returning
 // atomic per (wavefront, destination tile) on the bucket's count, lane slots
 // from the ballot.  Slots beyond the bucket's capacity go to the next list instead
 // (one atomic per wavefront).  Wave-uniform control flow.
-__device__ __forceinline__ void scatter_survivors(bool surv, uint32_t key, const PState& st, uint32_t id,
-                                                  const TileOut& o) {
-    const int lane = threadIdx.x % WAVE;
+__device__ __forceinline__ void scatter_survivors(uint32_t tid, bool surv, uint32_t key, const PState& st,
+                                                  uint32_t id, const TileOut& o) {
+    const int lane = (int)(tid % WAVE);
     const unsigned long long below = (1ull << lane) - 1ull;
     unsigned long long pending = __ballot(surv);
     uint32_t slot = 0;
@@ -97,9 +103,9 @@ __device__ __forceinline__ void scatter_survivors(bool surv, uint32_t key, const
 }
 
 // Append particles to a list, one atomic per wavefront (wave-uniform).
-__device__ __forceinline__ void append_list(bool on, const PState& st, uint32_t id, PState* pos, uint32_t* ids,
-                                            uint32_t* count) {
-    const int lane = threadIdx.x % WAVE;
+__device__ __forceinline__ void append_list(uint32_t tid, bool on, const PState& st, uint32_t id, PState* pos,
+                                            uint32_t* ids, uint32_t* count) {
+    const int lane = (int)(tid % WAVE);
     const unsigned long long m = __ballot(on);
     if (!m) return;
     const int leader = __ffsll((long long)m) - 1;
@@ -113,49 +119,25 @@ __device__ __forceinline__ void append_list(bool on, const PState& st, uint32_t 
     }
 }
 
-// Workgroup totals of particle-steps and survivors into the XCD's counters
-// (NT threads per workgroup).
-template <int NT>
-__device__ __forceinline__ void add_totals(uint32_t steps, uint32_t surv, unsigned long long* psteps,
-                                           uint32_t* live, uint32_t* s_red, int W = NT / WAVE) {
-    const int wave = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
-#pragma unroll
-    for (int o = WAVE / 2; o > 0; o >>= 1) {
-        steps += __shfl_xor(steps, o);
-        surv += __shfl_xor(surv, o);
-    }
-    __syncthreads();
-    if (lane == 0) {
-        s_red[wave] = steps;
-        s_red[NT / WAVE + wave] = surv;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned long long ts = 0;
-        uint32_t tl = 0;
-        for (int w = 0; w < W; ++w) {
-            ts += s_red[w];
-            tl += s_red[NT / WAVE + w];
-        }
-        const int xcd = blockIdx.x % NSEG;
-        if (ts) atomicAdd(&psteps[xcd * PSTRIDE], ts);
-        if (tl) atomicAdd(&live[xcd * CSTRIDE], tl);
-    }
+// Particles that ended in this step: off the live count, and the steps that
+// each attempted since it entered the tile layout onto the step total (the
+// live ones' attempts are known from the steps done).  Only workgroups in
+// which a particle ended touch the shared counters.
+__device__ __forceinline__ void add_ended(const TileStepArgs& a, uint32_t ended) {
+    const int xcd = blockIdx.x % NSEG;
+    atomicAdd(&a.psteps[xcd * PSTRIDE], (unsigned long long)ended * a.attempts);
+    atomicSub(&a.live[xcd * CSTRIDE], ended);
+}
+
+// The same for a wavefront of the list (wave-uniform).
+__device__ __forceinline__ void list_ended(const TileStepArgs& a, bool ended) {
+    const unsigned long long m = __ballot(ended);
+    if (m && threadIdx.x % WAVE == 0) add_ended(a, (uint32_t)__popcll(m));
 }
 
 __device__ __forceinline__ void end_record(const TileStepArgs& a, int status, uint32_t id, const double x[3], int rec) {
     a.rec_pos[id] = pack(x);
     a.rec_meta[id] = (status << META_SHIFT) | a.step0 | (rec && status == S_TERMINATED ? META_EXITPT : 0);
-}
-
-__device__ __forceinline__ void tile_coords(const Geom& g, const TileGeom& tg, const double x[3], int t[3]) {
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        int v = (int)floor(x[d]);
-        v = v > g.n[d] - 2 ? g.n[d] - 2 : v;
-        v = v < 0 ? 0 : v;
-        t[d] = v / tg.T[d];
-    }
 }
 
 // Bucket of each neighbour of tile ts (direction (dx, dy, dz) in -1..1 at
@@ -174,43 +156,52 @@ __device__ __forceinline__ int32_t neighbour_bucket(const TileGeom& tg, const Ti
     return b;
 }
 
+// Direction (0..26, as in neighbour_bucket) of tile td from tile ts; 27: not a
+// neighbour.
+__device__ __forceinline__ int tile_dir(const int ts[3], const int td[3]) {
+    const unsigned dx = (unsigned)(td[0] - ts[0] + 1), dy = (unsigned)(td[1] - ts[1] + 1),
+                   dz = (unsigned)(td[2] - ts[2] + 1);
+    return ((dx <= 2u) & (dy <= 2u) & (dz <= 2u)) ? (int)(dz * 9u + dy * 3u + dx) : 27;
+}
+
+struct ScatterLds {
+    uint32_t hist[32];  // survivors per direction (zeroed by the caller, before a barrier)
+    uint32_t base[32];
+    int32_t nb[32];     // neighbour buckets (written by the caller, before a barrier)
+    uint32_t ended;     // particles that ended in this batch (zeroed with hist)
+};
+
 // Survivors of one workgroup batch into the buckets of the next step.  A
-// survivor ends in its own tile or a neighbour (direction dx, dy, dz in
-// -1..1) unless it jumped further: ranks per direction from LDS atomics, then
-// one global atomic per (batch, destination tile) reserves the slots.
-// Survivors that jumped further take one global atomic each; slots beyond the
-// bucket's capacity go to the next list.  Block-uniform (barriers inside);
-// nb: the neighbour bucket of direction threadIdx.x (threads 0..26, from
-// neighbour_bucket), stored to s_nb before the first barrier.
-__device__ __forceinline__ void scatter_block(bool surv, const int ts[3], const int td[3], const PState& st,
-                                              uint32_t id, const TileGeom& tg, const TileOut& o, uint32_t* s_hist,
-                                              uint32_t* s_base, int32_t* s_nb, int32_t nb) {
-    int dir = 27;
-    if (surv) {
-        const int dx = td[0] - ts[0], dy = td[1] - ts[1], dz = td[2] - ts[2];
-        if (dx >= -1 && dx <= 1 && dy >= -1 && dy <= 1 && dz >= -1 && dz <= 1) dir = (dz + 1) * 9 + (dy + 1) * 3 + dx + 1;
-    }
-    if (threadIdx.x < 27) {
-        s_hist[threadIdx.x] = 0u;
-        s_nb[threadIdx.x] = nb;
-    }
-    __syncthreads();
+// survivor ends in its own tile or a neighbour unless it jumped further: ranks
+// per direction from LDS atomics, then one global atomic per (batch,
+// destination tile) reserves the slots.  Survivors that jumped further take
+// one global atomic each; slots beyond the bucket's capacity go to the next
+// list.  Block-uniform (barriers inside).
+__device__ __forceinline__ void scatter_block(const TileStepArgs& a, uint32_t tid, bool surv, bool ended,
+                                              const int ts[3], const int td[3], const PState& st, uint32_t id,
+                                              ScatterLds& s) {
+    const TileOut& o = a.out;
+    const int dir = surv ? tile_dir(ts, td) : 27;
     uint32_t rank = 0;
-    if (surv && dir < 27) rank = atomicAdd(&s_hist[dir], 1u);
+    if (surv && dir < 27) rank = atomicAdd(&s.hist[dir], 1u);
+    const unsigned long long em = __ballot(ended);
+    if (em && tid % WAVE == 0) atomicAdd(&s.ended, (uint32_t)__popcll(em));
     __syncthreads();
-    if (threadIdx.x < 27) {
-        const uint32_t c = s_hist[threadIdx.x];
-        s_base[threadIdx.x] = c ? atomicAdd(&o.tc[s_nb[threadIdx.x]], c) : 0u;
+    if (tid < 27) {
+        const uint32_t c = s.hist[tid];
+        s.base[tid] = c ? atomicAdd(&o.tc[s.nb[tid]], c) : 0u;
+    } else if (tid == 27) {
+        if (s.ended) add_ended(a, s.ended);
     }
     __syncthreads();
     bool over = false;
     if (surv) {
         uint32_t bkt, slot;
         if (dir < 27) {
-            bkt = (uint32_t)s_nb[dir];
-            slot = s_base[dir] + rank;
+            bkt = (uint32_t)s.nb[dir];
+            slot = s.base[dir] + rank;
         } else {
-            bkt = (uint32_t)o.slot_of[td[0] + tg.nt[0] * (td[1] + tg.nt[1] * td[2])];
+            bkt = (uint32_t)o.slot_of[td[0] + a.tg.nt[0] * (td[1] + a.tg.nt[1] * td[2])];
             slot = atomicAdd(&o.tc[bkt], 1u);
         }
         over = slot >= o.cap;
@@ -220,17 +211,14 @@ __device__ __forceinline__ void scatter_block(bool surv, const int ts[3], const 
             o.bid[q] = id;
         }
     }
-    append_list(over, st, id, o.list_pos, o.list_id, o.list_count);
+    append_list(tid, over, st, id, o.list_pos, o.list_id, o.list_count);
 }
 
 // ---------------------------------------------------------------------------
 // The staging box of tile t: the tile's cells plus a halo of H cells, clipped
 // to the block (lo: first point per axis, ext: points per axis, <= S).
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void tile_box(const Geom& g, const TileGeom& tg, int t, int tc[3], int lo[3], int ext[3]) {
-    tc[0] = t % tg.nt[0];
-    tc[1] = (t / tg.nt[0]) % tg.nt[1];
-    tc[2] = t / (tg.nt[0] * tg.nt[1]);
+__device__ __forceinline__ void tile_box(const Geom& g, const TileGeom& tg, const int tc[3], int lo[3], int ext[3]) {
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         const int l = tc[d] * tg.T[d] - tg.H;
@@ -292,153 +280,192 @@ struct StageRegs {
     }
 };
 
-// One RK4 step of up to one batch of a tile's particles and the move of the
-// survivors to their next buckets (block-uniform).
-template <int DT, int MODE, int REC, class CA>
-__device__ __forceinline__ void tile_batch(const TileStepArgs& a, bool alive, const PState& st, uint32_t id,
-                                           const int tc[3], const char* V0, const char* V1, CA& A, CA& B,
-                                           uint32_t& my_steps, uint32_t& my_surv, uint32_t* s_hist,
-                                           uint32_t* s_base, int32_t* s_nb, int32_t nb) {
-    double x[3] = {0.0, 0.0, 0.0};
-    int status = S_DEFER;
-    if (alive) {
-        unpack(st, x);
-        const auto on_exit = [&](const double* y) {
-            if constexpr (REC)
-                a.rec_out[id] = make_float4((float)(y[0] - x[0]), (float)(y[1] - x[1]), (float)(y[2] - x[2]), 0.f);
-        };
-        A.base = B.base = NO_CELL;
-        status = rk4_step<DT, MODE>(a.g, V0, V1, a.h, x, A, B, on_exit);
-        if (status != S_DEFER) ++my_steps;
-        if (status == S_TERMINATED || status == S_INVALID) end_record(a, status, id, x, REC);
-    }
-    const bool surv = alive && status == S_VALID;
-    const bool defer = alive && status == S_DEFER;
-    my_surv += surv ? 1u : 0u;
-    int td[3] = {0, 0, 0};
-    if (surv) tile_coords(a.g, a.tg, x, td);
-    scatter_block(surv, tc, td, surv ? pack(x) : st, id, a.tg, a.out, s_hist, s_base, s_nb, nb);
-    append_list(defer, st, id, a.list_pos, a.list_id, a.list_count);
+// A particle state as four registers (the compiler keeps the struct's array in
+// memory where it crosses a branch).
+typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+
+// A table entry read through the scalar cache (constant during the launch, the
+// same for the whole wavefront).
+template <class T>
+__device__ __forceinline__ T scalar_load(const T* p) {
+    using C = const __attribute__((address_space(4))) T*;
+    return *(C)(uintptr_t)p;
 }
 
-// Lanes of one batch reordered by the (z, y) row of their cell inside the
-// tile (counting sort in LDS), so that the lanes of a wavefront share grid
-// rows: each row load of the sampler then touches a few cache lines per
-// wavefront instead of one per lane.  Block-uniform.
-constexpr int SORT_ROWS_MAX = 16 * 16;  // rows of the largest tile (y, z sides <= 16)
-template <int NT>
-struct SortLds {
-    uint32_t off[SORT_ROWS_MAX + 64];
-    PState pos[NT];
-    uint32_t id[NT];
-};
+__device__ __forceinline__ void unpack_tile(int32_t t, int tc[3]) {
+    tc[0] = t & 1023;
+    tc[1] = (t >> 10) & 1023;
+    tc[2] = t >> 20;
+}
 
-template <int NT>
-__device__ __forceinline__ void sort_rows(const TileGeom& tg, const int tc[3], bool on, PState& st, uint32_t& id,
-                                          SortLds<NT>& s, int nthr = NT) {
-    const int Ty = tg.T[1], Tz = tg.T[2];
-    const int nrow = Ty * Tz;  // bin nrow: lanes without a particle, last
-    uint32_t key = (uint32_t)nrow;
-    if (on) {
-        int ly = (int)((st.cell >> 10) & 1023u) - tc[1] * Ty;
-        int lz = (int)(st.cell >> 20) - tc[2] * Tz;
-        ly = ly < 0 ? 0 : (ly > Ty - 1 ? Ty - 1 : ly);
-        lz = lz < 0 ? 0 : (lz > Tz - 1 ? Tz - 1 : lz);
-        key = (uint32_t)(lz * Ty + ly);
-    }
-    for (int i = threadIdx.x; i <= nrow; i += nthr) s.off[i] = 0u;
-    __syncthreads();
-    const uint32_t rank = atomicAdd(&s.off[key], 1u);
-    __syncthreads();
-    if (threadIdx.x < WAVE) {
-        // exclusive scan of the nrow + 1 bin counts by one wavefront
-        constexpr int PER = (SORT_ROWS_MAX + WAVE) / WAVE;
-        uint32_t v[PER], sum = 0;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int i = threadIdx.x * PER + k;
-            v[k] = i <= nrow ? s.off[i] : 0u;
-            sum += v[k];
-        }
-        uint32_t incl = sum;
-#pragma unroll
-        for (int o = 1; o < WAVE; o <<= 1) {
-            const uint32_t u = __shfl_up(incl, o);
-            if ((int)threadIdx.x >= o) incl += u;
-        }
-        uint32_t run = incl - sum;
-#pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int i = threadIdx.x * PER + k;
-            if (i <= nrow) s.off[i] = run;
-            run += v[k];
-        }
-    }
-    __syncthreads();
-    const uint32_t dst = s.off[key] + rank;
-    s.pos[dst] = st;
-    s.id[dst] = id;
-    __syncthreads();
-    st = s.pos[threadIdx.x];
-    id = s.id[threadIdx.x];
+// Inclusive sum over the wavefront.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+    const auto dpp = [](uint32_t x, auto ctrl, auto rows) {
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, decltype(ctrl)::value, decltype(rows)::value, 0xF, false);
+    };
+    using std::integral_constant;
+    constexpr integral_constant<int, 0xF> all{};
+    v += dpp(v, integral_constant<int, 0x111>{}, all);                             // row_shr:1
+    v += dpp(v, integral_constant<int, 0x112>{}, all);                             // row_shr:2
+    v += dpp(v, integral_constant<int, 0x114>{}, all);                             // row_shr:4
+    v += dpp(v, integral_constant<int, 0x118>{}, all);                             // row_shr:8
+    v += dpp(v, integral_constant<int, 0x142>{}, integral_constant<int, 0xA>{});   // row_bcast:15 into rows 1, 3
+    v += dpp(v, integral_constant<int, 0x143>{}, integral_constant<int, 0xC>{});   // row_bcast:31 into rows 2, 3
+    return v;
 }
 
 // ---------------------------------------------------------------------------
 // Gathering tile step: one workgroup of NT threads per tile, the particles
 // gather from the grids (through L2, which the tile order keeps warm).
+//
+// The particles of a batch are first reordered by the (z, y) row of their
+// cell inside the tile (counting sort in LDS), so that the lanes of a
+// wavefront share grid rows: each row load of the sampler then touches a few
+// cache lines per wavefront instead of one per lane (without it 6 to 10%
+// slower; a finer order along x changes nothing).  A tile has one row per
+// lane, so every wavefront scans the row counts by itself.
+//
+// What bounds it: the L1 returns in order, so a load behind one that missed to
+// HBM waits; accesses (0.38 per cycle and CU on the 512^3 f16 block) and
+// stalls on pending lines (0.63) fill every cycle.  The kernel therefore gains
+// from less work per wavefront and more wavefronts to hide it: 91 registers
+// leave 5 wavefronts per SIMD (f16; FP32 94; 127 and 121 before).  What is
+// computed from the thread index is computed anew behind the step for that
+// reason.  Nothing else is shared between workgroups than the buckets: the
+// live and step totals are touched only where a particle ended.
+// A 20-step interval of the 512^3 f16 block: 20.3 ms before, 17.3 now; 256^3,
+// 25 steps: f32 4.79 -> 4.33 ms, bf16 3.90 -> 2.82, f16 3.31 -> 2.76.
+// Prefetching a later tile's lines into L2 (every line of it by one dword
+// load, 16 to 128 tiles ahead) made it 8 to 14% slower: the loads wait in the
+// same in-order L1, and a third of the lines were evicted before their use.
 // ---------------------------------------------------------------------------
 template <int DT, int MODE, int REC, int NT>
 __global__ __launch_bounds__(NT) void tile_gather_kernel(const TileStepArgs a) {
-    __shared__ uint32_t s_red[2 * (NT / WAVE)];
-    __shared__ uint32_t s_hist[32], s_base[32];
-    __shared__ int32_t s_nb[32];
-    __shared__ SortLds<NT> s_sort;
-    if (blockIdx.x == 0 && threadIdx.x < NSEG) a.live_clear[threadIdx.x * CSTRIDE] = 0u;
-    if (blockIdx.x == 0 && threadIdx.x == NSEG) *a.list_clear = 0u;
-    // bucket b = this workgroup: its tile, count and first particles load at once
-    const uint32_t b = blockIdx.x;
-    const int32_t t = a.order[b];
-    uint32_t cnt = a.tc_in[b];
-    const size_t bin = (size_t)b * a.out.cap;
-    PState st0{};
-    uint32_t id0 = 0;
-    if (threadIdx.x < a.out.cap) {  // in the bucket even when beyond its count
-        st0 = a.in_pos[bin + threadIdx.x];
-        id0 = a.in_id[bin + threadIdx.x];
+    constexpr int Ty = TILE_GATHER[1], Tz = TILE_GATHER[2];
+    static_assert(Ty * Tz == WAVE, "one row of the tile per lane");
+    __shared__ ScatterLds s_sc;
+    __shared__ uint32_t s_row[WAVE];
+    __shared__ U4 s_pos[NT];
+    __shared__ uint32_t s_id[NT];
+    const uint32_t tid = threadIdx.x;
+    const uint32_t ntile = (uint32_t)a.order_len;
+    const bool list = blockIdx.x >= ntile;  // the workgroups behind the tiles' take the list
+    if (blockIdx.x == 0 && tid == 0) *a.list_clear = 0u;
+    // batches of NT particles [i, i + NT) of src_pos, src_id, every `stride`, up to n
+    const U4* src_pos = reinterpret_cast<const U4*>(a.list_pos);
+    const uint32_t* src_id = a.list_id;
+    uint32_t i = (blockIdx.x - ntile) * NT, n, stride = (gridDim.x - ntile) * NT;
+    // one state and id per thread, held as plain registers (an index past the
+    // last particle reads the last one's); a tile's first ones load before its
+    // count is known
+    U4 st;
+    uint32_t id;
+    const auto load = [&](uint32_t last) {
+        const uint32_t k = i + threadIdx.x < last ? i + threadIdx.x : last;
+        st = src_pos[k];
+        id = src_id[k];
+    };
+    int tc[3] = {0, 0, 0};
+    int32_t nb = -1;
+    if (list) {
+        n = scalar_load(a.list_count);
+        if (i >= n) return;
+        load(n - 1u);
+    } else {
+        // the bucket of this workgroup: its tile, count and first particles load at
+        // once.  Every other step runs each XCD's tiles backwards: what the last
+        // step touched last -- level n + 1, which is this step's level n, and the
+        // buckets it filled -- is then read first, while the memory-side cache
+        // still holds it.
+        const uint32_t b = a.backwards ? (ntile / NSEG - 1u - blockIdx.x / NSEG) * NSEG + blockIdx.x % NSEG : blockIdx.x;
+        int32_t t = scalar_load(a.order + b);
+        n = scalar_load(a.tc_in + b);
+        src_pos = reinterpret_cast<const U4*>(a.in_pos) + (size_t)b * a.out.cap;
+        src_id = a.in_id + (size_t)b * a.out.cap;
+        i = 0;
+        stride = NT;
+        load(a.out.cap - 1u);
+        asm("" : "+s"(t), "+s"(n));  // both tables' entries in flight before the first is looked at
+        if (t < 0) return;
+        if (tid == 0) a.tc_clear[b] = 0u;
+        n = n < a.out.cap ? n : a.out.cap;
+        if (n == 0) return;
+        // A tile with fewer particles than threads: the wavefronts past its count
+        // end here, so they hold no wave slot while the tile runs (s_barrier then
+        // waits for the surviving wavefronts only).  The wave index is taken from
+        // the first lane so that the branch is scalar: the whole wavefront ends.
+        if (n < (uint32_t)NT && __builtin_amdgcn_readfirstlane((int)(tid / WAVE)) >= (int)((n + WAVE - 1) / WAVE)) return;
+        unpack_tile(t, tc);
+        nb = neighbour_bucket(a.tg, a.out, tc);
     }
-    if (t < 0) return;
-    if (threadIdx.x == 0) a.tc_clear[b] = 0u;
-    cnt = cnt < a.out.cap ? cnt : a.out.cap;
-    if (cnt == 0) return;
-    // A tile with fewer particles than threads: the wavefronts past its count
-    // end here, so they hold no wave slot while the tile runs (s_barrier then
-    // waits for the surviving wavefronts only).  The wave index is taken from
-    // the first lane so that the branch is scalar: the whole wavefront ends.
-    int nw = NT / WAVE;
-    if (cnt < (uint32_t)NT) {
-        nw = (int)((cnt + WAVE - 1) / WAVE);
-        if (__builtin_amdgcn_readfirstlane((int)(threadIdx.x / WAVE)) >= nw) return;
-    }
-    int tc[3], lo[3], ext[3];
-    tile_box(a.g, a.tg, t, tc, lo, ext);
-    const int32_t nb = neighbour_bucket(a.tg, a.out, tc);
-    if (cnt <= NT) sort_rows<NT>(a.tg, tc, threadIdx.x < cnt, st0, id0, s_sort, nw * WAVE);
     const char* V0 = in_global(a.f0);
     const char* V1 = in_global(a.f1);
-    uint32_t my_steps = 0, my_surv = 0;
-    for (uint32_t bb = 0; bb < cnt; bb += NT) {
-        const uint32_t i = bb + threadIdx.x;
-        const bool alive = i < cnt;
-        PState st = st0;
-        uint32_t id = id0;
-        if (bb && alive) {
-            st = a.in_pos[bin + i];
-            id = a.in_id[bin + i];
+    bool first = true;
+    for (;;) {
+        // the thread index anew before and after the step: what is computed from
+        // it is then not held in registers across the step
+        uint32_t tid = opaque(threadIdx.x);
+        const bool alive = i + tid < n;
+        if (!list) {
+            if (tid < WAVE) s_row[tid] = 0u;
+            if (tid < 32) s_sc.hist[tid] = 0u;
+            if (tid == 0) s_sc.ended = 0u;
+            __syncthreads();
+            uint32_t row = 0, rank = 0;
+            if (alive) {
+                int ly = (int)((st.x >> 10) & 1023u) - tc[1] * Ty;
+                int lz = (int)(st.x >> 20) - tc[2] * Tz;
+                ly = ly > Ty - 1 ? Ty - 1 : ly;  // a point on the high face has the cell index n - 1
+                lz = lz > Tz - 1 ? Tz - 1 : lz;
+                row = (uint32_t)(lz * Ty + ly);
+                rank = atomicAdd(&s_row[row], 1u);
+            }
+            __syncthreads();
+            const uint32_t c = s_row[tid % WAVE];
+            const uint32_t dst = __shfl(wave_scan(c) - c, (int)row) + rank;
+            if (alive) {
+                s_pos[dst] = st;
+                s_id[dst] = id;
+            }
+            if (first && tid < 27) s_sc.nb[tid] = nb;
+            first = false;
+            nb = 0;
+        } else {
+            s_pos[tid] = st;
+            s_id[tid] = id;
         }
-        CellCache<DT> A, B;
-        tile_batch<DT, MODE, REC>(a, alive, st, id, tc, V0, V1, A, B, my_steps, my_surv, s_hist, s_base, s_nb, nb);
+        __syncthreads();
+        double x[3] = {0.0, 0.0, 0.0};
+        int status = S_INVALID;
+        if (alive) {
+            const U4 p = s_pos[tid];
+            unpack(PState{p.x, {p.y, p.z, p.w}}, x);
+            const auto on_exit = [&](const double* y) {
+                if constexpr (REC)
+                    a.rec_out[s_id[tid]] =
+                        make_float4((float)(y[0] - x[0]), (float)(y[1] - x[1]), (float)(y[2] - x[2]), 0.f);
+            };
+            GatherCache<DT> A, B;
+            forget(A);
+            forget(B);
+            status = rk4_step_gather<DT, MODE>(a.g, V0, V1, a.hs, x, A, B, false, on_exit);
+        }
+        tid = opaque(threadIdx.x);
+        id = s_id[tid];
+        const bool was = i + tid < n, surv = was & (status == S_VALID), ended = was & !surv;
+        if (ended) end_record(a, status, id, x, REC);
+        int td[3];
+        tile_coords<true>(a.g, a.tg, x, td);
+        if (!list) {
+            scatter_block(a, tid, surv, ended, tc, td, pack(x), id, s_sc);
+        } else {
+            list_ended(a, ended);
+            scatter_survivors(tid, surv, tile_index(a.tg, td), pack(x), id, a.out);
+        }
+        i += stride;
+        if (i >= n) break;
+        load(n - 1u);
     }
-    add_totals<NT>(my_steps, my_surv, a.psteps, a.live_out, s_red, nw);
 }
 
 // ---------------------------------------------------------------------------
@@ -450,15 +477,12 @@ __global__ __launch_bounds__(NT) void tile_gather_kernel(const TileStepArgs a) {
 template <int DT, int MODE, int REC, int S>
 __global__ __launch_bounds__(BLOCK) void tile_stage_kernel(const TileStepArgs a) {
     extern __shared__ __align__(16) char lds[];
-    __shared__ uint32_t s_red[2 * (BLOCK / WAVE)];
-    __shared__ uint32_t s_hist[32], s_base[32];
-    __shared__ int32_t s_nb[32];
+    __shared__ ScatterLds s_sc;
     using SR = StageRegs<DT, MODE, S>;
-    if (blockIdx.x == 0 && threadIdx.x < NSEG) a.live_clear[threadIdx.x * CSTRIDE] = 0u;
-    if (blockIdx.x == 0 && threadIdx.x == NSEG) *a.list_clear = 0u;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.list_clear = 0u;
     const uint32_t b = blockIdx.x;
-    const int32_t t = a.order[b];
-    uint32_t cnt = a.tc_in[b];
+    const int32_t t = scalar_load(a.order + b);
+    uint32_t cnt = scalar_load(a.tc_in + b);
     const size_t bin = (size_t)b * a.out.cap;
     PState st0{};
     uint32_t id0 = 0;
@@ -471,14 +495,15 @@ __global__ __launch_bounds__(BLOCK) void tile_stage_kernel(const TileStepArgs a)
     cnt = cnt < a.out.cap ? cnt : a.out.cap;
     if (cnt == 0) return;
     int tc[3], lo[3], ext[3];
-    tile_box(a.g, a.tg, t, tc, lo, ext);
+    unpack_tile(t, tc);
+    tile_box(a.g, a.tg, tc, lo, ext);
     const int32_t nb = neighbour_bucket(a.tg, a.out, tc);
     {
         SR sr;
         sr.load(a.g, in_global(a.f0), in_global(a.f1), lo, ext);
         sr.store(lds);
     }
-    __syncthreads();
+    if (threadIdx.x < 27) s_sc.nb[threadIdx.x] = nb;
     LdsCache<DT> A, B;
     A.plane = lds;
     B.plane = lds + (is_frozen<MODE> ? 0u : SR::PLANE);
@@ -488,8 +513,10 @@ __global__ __launch_bounds__(BLOCK) void tile_stage_kernel(const TileStepArgs a)
         A.lim[d] = B.lim[d] = ext[d] - 2;
     }
     A.S = B.S = S;
-    uint32_t my_steps = 0, my_surv = 0;
     for (uint32_t bb = 0; bb < cnt; bb += BLOCK) {
+        if (threadIdx.x < 32) s_sc.hist[threadIdx.x] = 0u;
+        if (threadIdx.x == 0) s_sc.ended = 0u;
+        __syncthreads();
         const uint32_t i = bb + threadIdx.x;
         const bool alive = i < cnt;
         PState st = st0;
@@ -498,10 +525,26 @@ __global__ __launch_bounds__(BLOCK) void tile_stage_kernel(const TileStepArgs a)
             st = a.in_pos[bin + i];
             id = a.in_id[bin + i];
         }
-        tile_batch<DT, MODE, REC>(a, alive, st, id, tc, nullptr, nullptr, A, B, my_steps, my_surv, s_hist, s_base,
-                                  s_nb, nb);
+        double x[3] = {0.0, 0.0, 0.0};
+        int status = S_DEFER;
+        if (alive) {
+            unpack(st, x);
+            const auto on_exit = [&](const double* y) {
+                if constexpr (REC)
+                    a.rec_out[id] = make_float4((float)(y[0] - x[0]), (float)(y[1] - x[1]), (float)(y[2] - x[2]), 0.f);
+            };
+            forget(A);
+            forget(B);
+            status = rk4_step<DT, MODE>(a.g, nullptr, nullptr, a.h, x, A, B, on_exit);
+        }
+        const bool surv = alive && status == S_VALID;
+        const bool ended = status == S_TERMINATED || status == S_INVALID;
+        if (ended) end_record(a, status, id, x, REC);
+        int td[3];
+        tile_coords<false>(a.g, a.tg, x, td);
+        scatter_block(a, threadIdx.x, surv, ended, tc, td, surv ? pack(x) : st, id, s_sc);
+        append_list(threadIdx.x, alive && status == S_DEFER, st, id, a.list_pos, a.list_id, a.list_count);
     }
-    add_totals<BLOCK>(my_steps, my_surv, a.psteps, a.live_out, s_red);
 }
 
 // ---------------------------------------------------------------------------
@@ -510,9 +553,7 @@ __global__ __launch_bounds__(BLOCK) void tile_stage_kernel(const TileStepArgs a)
 // ---------------------------------------------------------------------------
 template <int DT, int MODE, int REC>
 __global__ __launch_bounds__(BLOCK) void tile_list_kernel(const TileListArgs a) {
-    __shared__ uint32_t s_red[2 * (BLOCK / WAVE)];
     const uint32_t n = *a.in_count;
-    uint32_t my_steps = 0, my_surv = 0;
     const char* V0 = in_global(a.s.f0);
     const char* V1 = in_global(a.s.f1);
     // wave-uniform loop over the list
@@ -528,22 +569,22 @@ __global__ __launch_bounds__(BLOCK) void tile_list_kernel(const TileListArgs a) 
             const PState st = a.in_pos[i];
             id = a.in_id[i];
             unpack(st, x);
-            CellCache<DT> A, B;
-            A.base = B.base = NO_CELL;
+            GatherCache<DT> A, B;
+            forget(A);
+            forget(B);
             const auto on_exit = [&](const double* y) {
                 if constexpr (REC)
                     a.s.rec_out[id] = make_float4((float)(y[0] - x[0]), (float)(y[1] - x[1]), (float)(y[2] - x[2]), 0.f);
             };
-            status = rk4_step<DT, MODE>(a.s.g, V0, V1, a.s.h, x, A, B, on_exit);
-            ++my_steps;
+            status = rk4_step_gather<DT, MODE>(a.s.g, V0, V1, a.s.hs, x, A, B, false, on_exit);
             if (status != S_VALID) end_record(a.s, status, id, x, REC);
         }
         const bool surv = alive && status == S_VALID;
-        my_surv += surv ? 1u : 0u;
-        const uint32_t key = surv ? tile_key(a.s.g, a.s.tg, x) : 0u;
-        scatter_survivors(surv, key, pack(x), id, a.s.out);
+        list_ended(a.s, alive && !surv);
+        int td[3];
+        tile_coords<false>(a.s.g, a.s.tg, x, td);
+        scatter_survivors(threadIdx.x, surv, tile_index(a.s.tg, td), pack(x), id, a.s.out);
     }
-    add_totals<BLOCK>(my_steps, my_surv, a.s.psteps, a.s.live_out, s_red);
 }
 
 // ---------------------------------------------------------------------------
@@ -567,9 +608,11 @@ __global__ __launch_bounds__(BLOCK) void tile_bin_kernel(const TileBinArgs a) {
             id = a.id[sbase + i];
             double x[3];
             unpack(st, x);
-            key = tile_key(a.g, a.tg, x);
+            int td[3];
+            tile_coords<false>(a.g, a.tg, x, td);
+            key = tile_index(a.tg, td);
         }
-        scatter_survivors(alive, key, st, id, a.out);
+        scatter_survivors(threadIdx.x, alive, key, st, id, a.out);
     }
 }
 
@@ -617,14 +660,17 @@ __global__ __launch_bounds__(BLOCK) void tile_live_kernel(const TileLiveArgs a) 
 // Launchers.
 // ---------------------------------------------------------------------------
 template <int DT, int MODE, int REC>
-static hipError_t launch_tile_step_t(const TileStepArgs& a, int stage, hipStream_t s) {
+static hipError_t launch_tile_step_t(const TileStepArgs& a, int list_blocks, hipStream_t s) {
+    hipLaunchKernelGGL((tile_gather_kernel<DT, MODE, REC, GATHER_NT>), dim3(a.order_len + list_blocks), dim3(GATHER_NT),
+                       0, s, a);
+    return hipGetLastError();
+}
+
+template <int DT, int MODE, int REC>
+static hipError_t launch_tile_stage_t(const TileStepArgs& a, hipStream_t s) {
     constexpr int S = DT == DT_F32 ? TILE_S_F32 : TILE_S_16;
     using SR = StageRegs<DT, MODE, S>;
     constexpr size_t lds = (size_t)SR::NL * SR::PLANE;
-    if (!stage) {
-        hipLaunchKernelGGL((tile_gather_kernel<DT, MODE, REC, GATHER_NT>), dim3(a.order_len), dim3(GATHER_NT), 0, s, a);
-        return hipGetLastError();
-    }
     // LDS beyond the default limit: raise the kernel's dynamic-LDS limit (on
     // the current device) before the launch
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(&tile_stage_kernel<DT, MODE, REC, S>),
@@ -650,7 +696,12 @@ static hipError_t tile_dispatch(int dtype, int mode, int rec, F&& f) {
         case MODE_LINEAR: return by_rec(dt, std::integral_constant<int, MODE_LINEAR>{});
         case MODE_FROZEN: return by_rec(dt, std::integral_constant<int, MODE_FROZEN>{});
         case MODE_LINEAR | MODE_FP64: return by_rec(dt, std::integral_constant<int, MODE_LINEAR | MODE_FP64>{});
-        default: return by_rec(dt, std::integral_constant<int, MODE_FROZEN | MODE_FP64>{});
+        case MODE_FROZEN | MODE_FP64: return by_rec(dt, std::integral_constant<int, MODE_FROZEN | MODE_FP64>{});
+        case MODE_LINEAR | MODE_WIDE: return by_rec(dt, std::integral_constant<int, MODE_LINEAR | MODE_WIDE>{});
+        case MODE_FROZEN | MODE_WIDE: return by_rec(dt, std::integral_constant<int, MODE_FROZEN | MODE_WIDE>{});
+        case MODE_LINEAR | MODE_FP64 | MODE_WIDE:
+            return by_rec(dt, std::integral_constant<int, MODE_LINEAR | MODE_FP64 | MODE_WIDE>{});
+        default: return by_rec(dt, std::integral_constant<int, MODE_FROZEN | MODE_FP64 | MODE_WIDE>{});
         }
     };
     switch (dtype) {
@@ -660,9 +711,16 @@ static hipError_t tile_dispatch(int dtype, int mode, int rec, F&& f) {
     }
 }
 
-hipError_t launch_tile_step(const TileStepArgs& a, int dtype, int mode, int rec, int stage, hipStream_t s) {
+hipError_t launch_tile_step(const TileStepArgs& a, int dtype, int mode, int rec, int list_blocks, hipStream_t s) {
     return tile_dispatch(dtype, mode, rec, [&](auto dt, auto md, auto rc) {
-        return launch_tile_step_t<decltype(dt)::value, decltype(md)::value, decltype(rc)::value>(a, stage, s);
+        return launch_tile_step_t<decltype(dt)::value, decltype(md)::value, decltype(rc)::value>(a, list_blocks, s);
+    });
+}
+
+hipError_t launch_tile_stage(const TileStepArgs& a, int dtype, int mode, int rec, hipStream_t s) {
+    // the staging loads address 64-bit as they are
+    return tile_dispatch(dtype, mode & ~MODE_WIDE, rec, [&](auto dt, auto md, auto rc) {
+        return launch_tile_stage_t<decltype(dt)::value, decltype(md)::value & ~MODE_WIDE, decltype(rc)::value>(a, s);
     });
 }
 
