@@ -7,12 +7,19 @@ namespace bto {
 // ---------------------------------------------------------------------------
 // Fused advection: K RK4 steps per particle, then compaction of survivors.
 // ---------------------------------------------------------------------------
-template <int DT, int LPP> struct CacheOf { using T = CellCache<DT>; };
-template <> struct CacheOf<DT_F32, 2> { using T = PairCache; };
+// The step of a variant: two lanes per particle, and extended-precision
+// sampling of FP32 grids, whose gathering step takes 137 registers where
+// rk4_step takes 127 (3 instead of 4 wavefronts per SIMD: 6% slower on a 160^3
+// turbulence block), use rk4_step.
+template <int DT, int LPP, int MODE>
+constexpr bool gathers = LPP == 1 && !(DT == DT_F32 && (MODE & MODE_FP64) != 0);
+template <int DT, int LPP, bool GATHER> struct CacheOf { using T = CellCache<DT>; };
+template <int DT> struct CacheOf<DT, 1, true> { using T = GatherCache<DT>; };
+template <> struct CacheOf<DT_F32, 2, false> { using T = PairCache; };
 
 template <int DT, int MODE, int LPP, int REC>
 __global__ __launch_bounds__(BLOCK) void advect_kernel(const AdvectArgs a) {
-    using Cache = typename CacheOf<DT, LPP>::T;
+    using Cache = typename CacheOf<DT, LPP, gathers<DT, LPP, MODE>>::T;
     constexpr int W = BLOCK / WAVE;
     constexpr int PPB = BLOCK / LPP;  // particles per workgroup batch
     const int seg = blockIdx.x % NSEG;
@@ -37,7 +44,8 @@ __global__ __launch_bounds__(BLOCK) void advect_kernel(const AdvectArgs a) {
         const bool alive = i < cnt;
         double x[3] = {0.0, 0.0, 0.0};
         Cache A, B;
-        A.base = B.base = NO_CELL;
+        forget(A);
+        forget(B);
         if constexpr (LPP == 2) A.h = B.h = half;
         uint32_t id = 0;
         int status = S_VALID;
@@ -52,16 +60,37 @@ __global__ __launch_bounds__(BLOCK) void advect_kernel(const AdvectArgs a) {
                     a.rec_out[id] = make_float4((float)(y[0] - x[0]), (float)(y[1] - x[1]), (float)(y[2] - x[2]), 0.f);
             };
             // two steps per iteration: the slots swap roles, so nothing is copied
+            const auto step = [&](int q, Cache& LA, Cache& LB) {
+                if constexpr (gathers<DT, LPP, MODE>) {
+                    // uniform over the launch: held in scalar registers
+                    StepSizes hs = step_sizes(a.g, a.h[q]);
+#pragma unroll
+                    for (int d = 0; d < 3; ++d) {
+                        hs.full[d] = uniform(hs.full[d]);
+                        hs.half[d] = uniform(hs.half[d]);
+                        hs.sixth[d] = uniform(hs.sixth[d]);
+                    }
+                    // One level at a time for 16-bit grids (256^3 turbulence, f16, re-sorted
+                    // every 5 steps: 3.10 ms per 25-step interval instead of 3.17) and for
+                    // one-step launches (128^3 ABC in situ: 15.0 us per call instead of 15.4);
+                    // both together for fused FP32 launches (128^3 ABC: 699 us instead of 708,
+                    // 256^3 turbulence 4.72 ms instead of 4.76).
+                    return rk4_step_gather<DT, MODE>(a.g, a.f[q], a.f[q + 1], hs, x, LA, LB, DT != DT_F32 || a.K == 1,
+                                                     on_exit);
+                } else {
+                    return rk4_step<DT, MODE>(a.g, a.f[q], a.f[q + 1], a.h[q], x, LA, LB, on_exit);
+                }
+            };
             for (s = 0; s < a.K; ++s) {
-                status = rk4_step<DT, MODE>(a.g, a.f[s], a.f[s + 1], a.h[s], x, A, B, on_exit);
+                status = step(s, A, B);
                 if (status != S_VALID) break;
-                A.base = NO_CELL;
-                if (is_frozen<MODE>) B.base = NO_CELL;
+                forget(A);
+                if (is_frozen<MODE>) forget(B);
                 if (++s >= a.K) break;
-                status = rk4_step<DT, MODE>(a.g, a.f[s], a.f[s + 1], a.h[s], x, B, A, on_exit);
+                status = step(s, B, A);
                 if (status != S_VALID) break;
-                B.base = NO_CELL;
-                if (is_frozen<MODE>) A.base = NO_CELL;
+                forget(B);
+                if (is_frozen<MODE>) forget(A);
             }
             if (owner) my_steps += (status == S_VALID) ? (uint32_t)a.K : (uint32_t)(s + 1);
         }
@@ -123,14 +152,18 @@ static auto with_rec(int rec, F&& f) {
 
 template <int DT, int LPP, class F>
 static auto with_mode_rec(int mode, int rec, F&& f) {
-    if constexpr (LPP == 2) {  // two lanes per particle: the FP32 sampler only
+    if constexpr (LPP == 2) {  // two lanes per particle: the FP32 sampler only, 64-bit offsets as they are
         return (mode & MODE_FROZEN) ? with_rec<DT, LPP, MODE_FROZEN>(rec, f) : with_rec<DT, LPP, MODE_LINEAR>(rec, f);
     } else {
         switch (mode) {
         case MODE_LINEAR: return with_rec<DT, LPP, MODE_LINEAR>(rec, f);
         case MODE_FROZEN: return with_rec<DT, LPP, MODE_FROZEN>(rec, f);
+        case MODE_LINEAR | MODE_WIDE: return with_rec<DT, LPP, MODE_LINEAR | MODE_WIDE>(rec, f);
+        case MODE_FROZEN | MODE_WIDE: return with_rec<DT, LPP, MODE_FROZEN | MODE_WIDE>(rec, f);
         case MODE_LINEAR | MODE_FP64: return with_rec<DT, LPP, MODE_LINEAR | MODE_FP64>(rec, f);
-        default: return with_rec<DT, LPP, MODE_FROZEN | MODE_FP64>(rec, f);
+        case MODE_FROZEN | MODE_FP64: return with_rec<DT, LPP, MODE_FROZEN | MODE_FP64>(rec, f);
+        case MODE_LINEAR | MODE_FP64 | MODE_WIDE: return with_rec<DT, LPP, MODE_LINEAR | MODE_FP64 | MODE_WIDE>(rec, f);
+        default: return with_rec<DT, LPP, MODE_FROZEN | MODE_FP64 | MODE_WIDE>(rec, f);
         }
     }
 }

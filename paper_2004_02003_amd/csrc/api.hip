@@ -750,7 +750,7 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
         return BTO_OK;
     }
     const int lpp = dtype == BTO_F32 ? c->lanes_per_particle : 1;
-    int per_cu = advect_max_blocks_per_cu(dtype, mode & ~MODE_WIDE, lpp, rec);
+    int per_cu = advect_max_blocks_per_cu(dtype, mode, lpp, rec);
     if (c->blocks_per_cu_cap > 0 && c->blocks_per_cu_cap < per_cu) per_cu = c->blocks_per_cu_cap;
     const int R = blocks_per_seg(c, max_seg * lpp, per_cu);
     // launches of (nearly) equal length, at most steps_per_launch steps each
@@ -798,7 +798,7 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
         a.rec_meta = c->rec_meta;
         a.rec_out = c->rec_out;
         a.psteps = c->psteps;
-        hipError_t e = launch_advect(a, dtype, mode & ~MODE_WIDE, lpp, rec, R, s);
+        hipError_t e = launch_advect(a, dtype, mode, lpp, rec, R, s);
         if (e != hipSuccess) return hip_fail(c, e, "advect launch");
         c->cur = 1 - c->cur;
         c->slot = (c->slot + 1) % 3;
