@@ -246,11 +246,12 @@ int bto_get_tuning(const bto_ctx *ctx, bto_tuning *t);
  * use of flow maps, Results section) and to the velocity grids.
  * For the seeds of the current interval (bto_seed*), recompute the RK4
  * advection through d_fields / times (same meaning as bto_advect_interval,
- * all n_steps + 1 grids resident), storing each particle's position every
- * ckpt_every steps, then sweep back segment by segment: recompute the
- * segment's steps from its checkpoint and apply the transposed stage
- * recurrences of RK4 with the trilinear sampler's gradient on the cell chosen
- * by the floor/clamp rule.
+ * all n_steps + 1 grids resident), keeping the cell and the in-cell offsets
+ * of every stage, then sweep back applying the transposed stage recurrences
+ * of RK4 with the trilinear sampler's gradient on the cell chosen by the
+ * floor/clamp rule.  An interval whose stages pass 1 GiB (64 bytes per step
+ * and seed) is swept in groups of segments of ckpt_every steps, each
+ * recomputed from the positions at its first step.
  *   d_cot_end  (n_seeds x n_cot x 3 floats, world units): cotangents of the
  *              end positions; n_cot = 1 (a scalar loss L = sum c . x_end) or
  *              3 (one per axis: d_grad_seed then holds the 3x3 flow-map
@@ -281,10 +282,10 @@ int bto_get_tuning(const bto_ctx *ctx, bto_tuning *t);
  * steps advected and ckpt_every the recorded spacing.  d_status then holds
  * the recorded flags.
  * Seeds that do not stay inside the block for the whole interval contribute
- * nothing: their gradient rows are zero.  Scratch of about
- * n_seeds * (n_steps / ckpt_every + ckpt_every) * 24 bytes is held by the
- * context.  The call waits for its small host-to-device tables to be copied
- * (it synchronizes `stream` once before the launch). */
+ * nothing: their gradient rows are zero.  Scratch of up to 1 GiB for the
+ * stages (less where that much memory is not free) and about
+ * n_seeds * n_steps / ckpt_every * 24 bytes for the positions is held by the
+ * context, grown on demand (a growth synchronizes `stream`). */
 int bto_adjoint_interval(bto_ctx *ctx, const void *const *d_fields, const double *times, int32_t n_steps,
                          int32_t dtype, int32_t flags, const float *d_cot_end, int32_t n_cot, float *d_grad_seed,
                          float *const *d_grad_fields, uint8_t *d_status, int32_t ckpt_every, void *stream);

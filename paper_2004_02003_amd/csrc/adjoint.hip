@@ -2,83 +2,42 @@
 // with respect to seed positions and velocity grids), with checkpointing, and
 // the FTLE of flow-map Jacobians.
 //
-// One lane per seed.  Forward: the same RK4 stepping as the advection kernel,
-// storing the FP64 position every `k` steps (checkpoints) -- or none at all
-// when the advection recorded the checkpoints (then the per-seed records give
-// which seeds stayed inside for the whole interval).  Backward: for each
-// k-step segment in reverse, recompute its steps from the checkpoint (storing
-// each step's start), then walk them backwards: recompute the four stage
-// points with the sampler gradients G_s (on the cell chosen by the floor/clamp
-// rule) and apply the transposed stage recurrences to every cotangent vector.
+// A reverse step needs the cell and the offsets of each of the step's four
+// stages, which only the step itself tells.  They are put on a tape (64 bytes
+// per step and seed), in one of two ways:
+//   * forward   one lane per seed steps through the whole interval from its
+//               position, as the advection does, and writes the tape of every
+//               step; where the tape would pass its budget, FP64 checkpoints
+//               every `k` steps instead;
+//   * recompute one lane per seed and checkpoint segment steps through the
+//               segment from its checkpoint (the forward's, or recorded by the
+//               advection; then the per-seed records say which seeds stayed
+//               inside for the whole interval).  Segments do not depend on
+//               each other, so as many as the tape holds run at once.
+// The reverse sweep then walks the tape backwards, one lane per seed: with
+// every stage's cell known beforehand, all the step's corner values load
+// together and a step ahead, the sampler gradients G_s follow (on the cell
+// chosen by the floor/clamp rule), and the transposed stage recurrences are
+// applied to every cotangent vector.
 // Grid gradients leave as records for the sorted, deterministic reduction
 // (grad_reduce.hip), or as FP32 atomics when no record buffer is given (their
-// summation order is then not fixed).  Terminated and invalid seeds contribute nothing (the
-// loss covers only the basis flows that stay inside the block).
+// summation order is then not fixed).  Terminated and invalid seeds contribute
+// nothing (the loss covers only the basis flows that stay inside the block).
+//
+// What bounds the sweeps at a few tens of thousands of seeds (three wavefronts
+// per CU) is the CU's L1: it keeps about 64 lines in flight, whatever the
+// wavefronts ask for.  So the reverse sweep asks for each line once: a lane
+// loads a stage's cell only where it differs from the neighbouring stage's, and
+// level n + 1 is kept from the step before; loading all six cells of a step
+// took 330 us instead of 223 (Jacobian of 48,960 seeds over 49 steps, 160 x 144
+// x 136 f16 turbulence) and 316 instead of 231 (gradient of 32,768 seeds over
+// 50 steps, 128^3 ABC, f32; 372 without the loads a step ahead).  The forward
+// takes 266 us there, the recompute of five segments 174.  One sweep that
+// recomputed and reversed one segment after the other, each step in dependent
+// loads, took 935 and 541 us in all.
 #include "bto_internal.h"
 
 namespace bto {
-
-struct StageRec {
-    uint32_t base[4];
-    float f[4][3];
-    float G[4][3][3];  // d k~_r / d y_d in cells (k~ = velocity in cells per unit time)
-};
-
-// One RK4 step that also records every stage's cell, offsets and sampler
-// gradient.  The stage velocities and positions come from the same sampler
-// calls in the same order as rk4_step (so the step is bit-identical to the
-// forward's and takes the same decisions); the gradient G of each stage is
-// taken separately on the same corner values.  Returns the same status.
-template <int DT, int MODE>
-__device__ __forceinline__ int rk4_step_rec(const Geom& g, const char* V0, const char* V1, double h,
-                                            Stepper<DT>& st, StageRec& rec) {
-    const double hs[3] = {h * g.inv_sp[0], h * g.inv_sp[1], h * g.inv_sp[2]};
-    float k[4][3];
-    double y[3] = {st.x[0], st.x[1], st.x[2]};
-    const double coef[3] = {0.5, 0.5, 1.0};
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        if (s > 0) {
-#pragma unroll
-            for (int d = 0; d < 3; ++d) y[d] = fma(coef[s - 1] * hs[d], (double)k[s - 1][d], st.x[d]);
-            if (!inside(g, y)) return S_TERMINATED;
-        }
-        const Cell c = locate(g, y);
-        rec.base[s] = c.base;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) rec.f[s][d] = c.f[d];
-        float G[3][3], unused[3];
-        if (is_frozen<MODE> || s == 0) {
-            ensure<DT>(g, V0, c.base, st.A);
-            trilerp(st.A, c.f, k[s]);
-            trilerp_grad<false>(st.A, st.A, c.f, unused, G);
-        } else if (s == 3) {
-            ensure<DT>(g, V1, c.base, st.B);
-            trilerp(st.B, c.f, k[s]);
-            trilerp_grad<false>(st.B, st.B, c.f, unused, G);
-        } else {
-            ensure<DT>(g, V0, c.base, st.A);
-            ensure<DT>(g, V1, c.base, st.B);
-            trilerp_mid(st.A, st.B, c.f, k[s]);
-            trilerp_grad<true>(st.A, st.B, c.f, unused, G);
-        }
-        if (!finite3(k[s])) return S_INVALID;
-#pragma unroll
-        for (int r = 0; r < 3; ++r)
-#pragma unroll
-            for (int d = 0; d < 3; ++d) rec.G[s][r][d] = (float)g.inv_sp[r] * G[r][d];
-    }
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const float ks = (k[0][d] + k[3][d]) + 2.0f * (k[1][d] + k[2][d]);
-        y[d] = fma(hs[d] * (1.0 / 6.0), (double)ks, st.x[d]);
-    }
-    if (!inside(g, y)) return S_TERMINATED;
-    st.x[0] = y[0];
-    st.x[1] = y[1];
-    st.x[2] = y[2];
-    return S_VALID;
-}
 
 __device__ __forceinline__ void gT(const float G[3][3], const float v[3], float out[3]) {
 #pragma unroll
@@ -89,14 +48,14 @@ __device__ __forceinline__ void gT(const float G[3][3], const float v[3], float 
 // Grid-gradient accumulator: the 8 corner gradients of one cell of one grid
 // level, summed in registers while consecutive stage contributions hit the
 // same cell and level, and flushed only when the cell or level changes (and at
-// the end of each checkpoint segment).  In the reverse sweep a level receives
+// the end of each launch).  In the reverse sweep a level receives
 // its contributions from two consecutive steps (level n from step n's first
 // three stages and from step n-1's last three), so a particle that stays in
 // its cell flushes once per level.  A flush appends a record for the sorted,
 // deterministic reduction (or, without records or when they are full, adds the
 // values to the grid with FP32 atomics).
 struct GradAcc {
-    uint32_t base;
+    uint32_t val;   // cell (first value's index; NO_CELL: none)
     int level;
     uint32_t nrec;  // records written by this seed
     float v[8][3];
@@ -104,49 +63,50 @@ struct GradAcc {
 
 __device__ __forceinline__ void acc_flush(const Geom& g, float* const* gf, const GradRec& R, uint32_t pid,
                                           GradAcc& A) {
-    if (A.base == NO_CELL) return;
+    if (A.val == NO_CELL) return;
     if (R.key && A.nrec < R.per_seed) {
         // the seed's next record slot: no counter, and the lanes of a wavefront
         // that flush together write neighbouring slots
         const uint64_t slot = (uint64_t)(A.nrec++) * R.P + pid;
-        const uint32_t i = A.base % g.sy, j = (A.base / g.sy) % (uint32_t)g.n[1], k = A.base / g.sz;
+        const uint32_t base = A.val / 3u;
+        const uint32_t i = base % g.sy, j = (base / g.sy) % (uint32_t)g.n[1], k = base / g.sz;
         const uint64_t colour = (uint64_t)((i & 1u) | ((j & 1u) << 1) | ((k & 1u) << 2));
         R.key[slot] = (colour << (R.level_bits + R.cell_bits)) | ((uint64_t)A.level << R.cell_bits) |
-                      (uint64_t)A.base;  // the slot's sort value, its index, was written by the clear
+                      (uint64_t)base;  // the slot's sort value, its index, was written by the clear
         float4* out = reinterpret_cast<float4*>(R.val + 24 * (size_t)slot);
 #pragma unroll
         for (int q = 0; q < 6; ++q)
             out[q] = make_float4(A.v[(4 * q) / 3][(4 * q) % 3], A.v[(4 * q + 1) / 3][(4 * q + 1) % 3],
                                  A.v[(4 * q + 2) / 3][(4 * q + 2) % 3], A.v[(4 * q + 3) / 3][(4 * q + 3) % 3]);
-        A.base = NO_CELL;
+        A.val = NO_CELL;
         return;
     }
-    float* grid = in_global(gf[A.level]);
+    float* grid = in_global(gf[A.level]) + A.val;
 #pragma unroll
     for (int c = 0; c < 2; ++c)
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
-                float* p = grid + 3 * ((uint64_t)A.base + (uint64_t)q + (uint64_t)g.sy * b + (uint64_t)g.sz * c);
+                float* p = grid + (size_t)(3u * q + g.sy3 * b + g.sz3 * c);
                 const int k = q + 2 * b + 4 * c;
                 unsafeAtomicAdd(p + 0, A.v[k][0]);
                 unsafeAtomicAdd(p + 1, A.v[k][1]);
                 unsafeAtomicAdd(p + 2, A.v[k][2]);
             }
-    A.base = NO_CELL;
+    A.val = NO_CELL;
 }
 
 __device__ __forceinline__ void acc_add(const Geom& g, float* const* gf, const GradRec& R, uint32_t pid, GradAcc& A,
-                                        int level, uint32_t base, const float f[3], float coef, const float lam[3]) {
-    if (A.base != base || A.level != level) {
+                                        int level, const TapeEntry& t, float coef, const float lam[3]) {
+    if (A.val != t.val || A.level != level) {
         acc_flush(g, gf, R, pid, A);
-        A.base = base;
+        A.val = t.val;
         A.level = level;
 #pragma unroll
         for (int k = 0; k < 8; ++k) A.v[k][0] = A.v[k][1] = A.v[k][2] = 0.f;
     }
-    const float wx[2] = {1.f - f[0], f[0]}, wy[2] = {1.f - f[1], f[1]}, wz[2] = {1.f - f[2], f[2]};
+    const float wx[2] = {1.f - t.f[0], t.f[0]}, wy[2] = {1.f - t.f[1], t.f[1]}, wz[2] = {1.f - t.f[2], t.f[2]};
     const float l[3] = {(float)g.inv_sp[0] * lam[0] * coef, (float)g.inv_sp[1] * lam[1] * coef,
                         (float)g.inv_sp[2] * lam[2] * coef};
 #pragma unroll
@@ -163,52 +123,104 @@ __device__ __forceinline__ void acc_add(const Geom& g, float* const* gf, const G
             }
 }
 
-// One wavefront per workgroup: the adjoint holds about 280 registers per lane
-// (one wavefront per SIMD), so a seed set of a few tens of thousands fills
+// One wavefront per workgroup: a seed set of a few tens of thousands fills
 // only a fraction of the SIMDs; single-wavefront workgroups spread those
 // wavefronts over every CU (and its L1 and texture pipeline) instead of
 // packing four of them onto each of the first P/256 CUs.
 constexpr int ADJ_BLOCK = WAVE;
 
-template <int DT, int MODE, int NCOT>
-__global__ __launch_bounds__(ADJ_BLOCK) void adjoint_kernel(const AdjointArgs a) {
-    const int64_t p = (int64_t)blockIdx.x * ADJ_BLOCK + threadIdx.x;
-    if (p >= a.P) return;
-    const int N = a.N, K = a.k;
-    const int nseg = (N + K - 1) / K;
-    // checkpoints and recomputed step starts, slot-major ([slot][seed][xyz]), so a
-    // wavefront's 64 positions of one slot are one contiguous 1.5 KB run
-    const size_t P3 = (size_t)a.P * 3;
-    const size_t CK = (size_t)a.ck_stride;
-    double* ck = a.ckpt + (size_t)p * 3;
-    double* buf = a.buf + (size_t)p * 3;
-    // grids, steps and gradient grids are given from step f_base on
-    const auto F = [&](int n) { return in_global(a.f[n - a.f_base]); };
-    const auto H = [&](int n) { return a.h[n - a.f_base]; };
-
-    Stepper<DT> st;
-    stepper_init(st);
-    int status;
-    if (a.rec_meta) {
-        // forward recorded by the advection: its checkpoints are in place and
-        // the record says whether the seed stayed inside for the whole interval
-        const int32_t meta = a.rec_meta[p];
-        status = meta == META_LIVE ? S_VALID : (int)((uint32_t)meta >> META_SHIFT);
-    } else {
+// Steps n0 .. n1 - 1 from st.x, the advection's own step; tape entries of step
+// n at t + 4 * np * (n - n0) (t null: none).  Returns the status of the step
+// that ended it, or S_VALID.
+template <int DT, int MODE>
+__device__ __forceinline__ int adj_steps(const AdjointArgs& a, double* x, int n0, int n1, TapeEntry* t, bool ck) {
+    GatherCache<DT> A, B;
+    forget(A);
+    forget(B);
+    int status = S_VALID;
+    const auto step = [&](int n, GatherCache<DT>& LA, GatherCache<DT>& LB) {
+        if (ck && n % a.k == 0) {
+            double* c = a.ckpt + a.ck_stride * (int64_t)(n / a.k) + 3 * (a.p0 + (int64_t)blockIdx.x * ADJ_BLOCK + threadIdx.x);
 #pragma unroll
-        for (int d = 0; d < 3; ++d) st.x[d] = (a.seed_xyz[3 * p + d] - a.origin[d]) * a.g.inv_sp[d];
-        status = inside(a.g, st.x) ? S_VALID : S_TERMINATED;
-        for (int n = 0; n < N && status == S_VALID; ++n) {
-            if (n % K == 0) {
-#pragma unroll
-                for (int d = 0; d < 3; ++d) ck[CK * (size_t)(n / K) + d] = st.x[d];
-            }
-            status = rk4_step_alt<DT, MODE>(a.g, F(n), F(n + 1), H(n), n, st);
+            for (int d = 0; d < 3; ++d) c[d] = x[d];
         }
+        StepSizes hs = step_sizes(a.g, scalar_load(a.h + (n - a.f_base)));
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            hs.full[d] = uniform(hs.full[d]);
+            hs.half[d] = uniform(hs.half[d]);
+            hs.sixth[d] = uniform(hs.sixth[d]);
+        }
+        const auto on_stage = [&](int s, const GatherCell<float>& c) {
+            if (t) {
+                const U4 e = {c.val, __float_as_uint(c.f[0]), __float_as_uint(c.f[1]), __float_as_uint(c.f[2])};
+                *reinterpret_cast<U4*>(t + a.np * (int64_t)(4 * (n - n0) + s)) = e;
+            }
+        };
+        status = rk4_step_gather<DT, MODE>(a.g, in_global(scalar_load(a.f + (n - a.f_base))),
+                                           in_global(scalar_load(a.f + (n + 1 - a.f_base))), hs, x, LA, LB, false,
+                                           [](const double*) {}, on_stage);
+        forget(LA);  // receives level n + 2
+        if (is_frozen<MODE>) forget(LB);
+    };
+    for (int n = n0; n < n1; ++n) {
+        step(n, A, B);
+        if (status != S_VALID || ++n >= n1) break;
+        step(n, B, A);
+        if (status != S_VALID) break;
     }
-    // a seed dropped by the call of a later segment stays dropped
-    const int prior = a.drop ? (int)a.drop[p] : 0;
+    return status;
+}
+
+template <int DT, int MODE>
+__global__ __launch_bounds__(ADJ_BLOCK) void adj_forward_kernel(const AdjointArgs a) {
+    const int64_t q = (int64_t)blockIdx.x * ADJ_BLOCK + threadIdx.x, p = a.p0 + q;
+    if (q >= a.np) return;
+    double x[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) x[d] = (a.seed_xyz[3 * p + d] - a.origin[d]) * a.g.inv_sp[d];
+    int status = S_TERMINATED;
+    if (inside(a.g, x)) status = adj_steps<DT, MODE>(a, x, 0, a.N, a.tape ? a.tape + q : nullptr, a.ckpt != nullptr);
+    a.status[p] = (uint8_t)status;
+    a.bad[p] = 0;
+}
+
+__device__ __forceinline__ int forward_status(const AdjointArgs& a, int64_t p) {
+    if (!a.rec_meta) return (int)a.status[p];
+    const int32_t meta = a.rec_meta[p];
+    return meta == META_LIVE ? S_VALID : (int)((uint32_t)meta >> META_SHIFT);
+}
+
+// Workgroup row y: segment sg_last + y.  A recomputed step that does not stay
+// inside contradicts the forward that called the seed valid: possible only
+// when the forward was taken by the advection with other rounding (recorded
+// checkpoints; launches cut inside a checkpoint segment, two lanes per
+// particle, the tile layout).  Such a seed is marked bad.
+template <int DT, int MODE>
+__global__ __launch_bounds__(ADJ_BLOCK) void adj_recompute_kernel(const AdjointArgs a) {
+    const int64_t q = (int64_t)blockIdx.x * ADJ_BLOCK + threadIdx.x, p = a.p0 + q;
+    if (q >= a.np || forward_status(a, p) != S_VALID) return;
+    const int sg = a.sg_last + (int)blockIdx.y, n0 = sg * a.k, n1 = n0 + a.k < a.N ? n0 + a.k : a.N;
+    double x[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) x[d] = a.ckpt[a.ck_stride * (int64_t)sg + 3 * p + d];
+    TapeEntry* t = a.tape + 4 * a.np * (int64_t)(n0 - a.sg_last * a.k) + q;
+    if (adj_steps<DT, MODE>(a, x, n0, n1, t, false) != S_VALID) a.bad[p] = 1;
+}
+
+template <int DT, int MODE, int NCOT>
+__global__ __launch_bounds__(ADJ_BLOCK) void adj_reverse_kernel(const AdjointArgs a) {
+    constexpr bool W = is_wide<MODE>;
+    const int64_t q = (int64_t)blockIdx.x * ADJ_BLOCK + threadIdx.x, p = a.p0 + q;
+    if (q >= a.np) return;
+    const int nseg = (a.N + a.k - 1) / a.k;
+    const int n_lo = a.sg_last * a.k, n_hi = (a.sg_first + 1) * a.k < a.N ? (a.sg_first + 1) * a.k : a.N;
     const bool first = a.sg_first == nseg - 1, last = a.sg_last == 0;
+    const int status = forward_status(a, p);
+    // a seed dropped by an earlier launch of the interval stays dropped
+    const int prior = a.drop && !first ? (int)a.drop[p] : 0;
+    const bool bad = status == S_VALID && !prior && a.bad[p];
+    const bool on = status == S_VALID && !prior && !bad;
 
     float lam[NCOT][3];
 #pragma unroll
@@ -216,88 +228,133 @@ __global__ __launch_bounds__(ADJ_BLOCK) void adjoint_kernel(const AdjointArgs a)
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             const float* src = first ? a.cot : a.lam;
-            lam[c][d] = status == S_VALID && !prior ? src[(p * NCOT + c) * 3 + d] * (first ? (float)a.sp[d] : 1.f)
-                                                    : 0.f;
+            lam[c][d] = on ? src[(p * NCOT + c) * 3 + d] * (first ? (float)a.sp[d] : 1.f) : 0.f;
         }
 
     GradAcc acc;
-    acc.base = NO_CELL;
+    acc.val = NO_CELL;
     acc.level = -1;
-    acc.nrec = 0;
-    // A recomputed step that does not stay inside contradicts the forward that
-    // called the seed valid: possible only when the forward was taken by the
-    // advection with other rounding (recorded checkpoints; launches cut inside a
-    // checkpoint segment, two lanes per particle, the tile layout).  Such a seed
-    // is dropped.
-    bool mismatch = false;
-    if (status == S_VALID && !prior) {
-        for (int sg = a.sg_first; sg >= a.sg_last && !mismatch; --sg) {
-            const int n0 = sg * K;
-            const int n1 = (n0 + K < N) ? n0 + K : N;
-            stepper_init(st);
+    acc.nrec = a.nrec && a.sg_first != a.call_first ? a.nrec[p] : 0u;
+    if (on) {
+        const TapeEntry* t = a.tape + q;
+        const auto read = [&](int n, TapeEntry* e) {
 #pragma unroll
-            for (int d = 0; d < 3; ++d) st.x[d] = ck[CK * (size_t)sg + d];
-            for (int n = n0; n < n1 && !mismatch; ++n) {
-#pragma unroll
-                for (int d = 0; d < 3; ++d) buf[P3 * (size_t)(n - n0) + d] = st.x[d];
-                if (n + 1 < n1) mismatch = rk4_step_alt<DT, MODE>(a.g, F(n), F(n + 1), H(n), n - n0, st) != S_VALID;
+            for (int s = 0; s < 4; ++s) {
+                const U4 w = *reinterpret_cast<const U4*>(t + a.np * (int64_t)(4 * (n - n_lo) + s));
+                e[s] = TapeEntry{w.x, {__uint_as_float(w.y), __uint_as_float(w.z), __uint_as_float(w.w)}};
             }
-            for (int n = n1 - 1; n >= n0 && !mismatch; --n) {
-                Stepper<DT> sr;
-                stepper_init(sr);
+        };
+        // A step's corner values: stage 1's cell on level n (S0); stages 2 and 3
+        // on levels n and n + 1, stage 4 on level n + 1, each only by the lanes
+        // whose cell there differs from the one it is taken from otherwise (the
+        // stage before it; on level n + 1 the stage after it, and for stage 4
+        // stage 1 of the step n + 1, still held in P).
+        GatherCache<DT> S0, A1, A2, B1, B2, B3, P;
+        const auto corners = [&](const char* V0, const char* V1, const TapeEntry* c) {
+            S0.template load<W>(a.g, V0, c[0].val);
+            if (c[1].val != c[0].val) A1.template load<W>(a.g, V0, c[1].val);
+            if (c[2].val != c[1].val) A2.template load<W>(a.g, V0, c[2].val);
+            if constexpr (is_frozen<MODE>) {
+                if (c[3].val != c[2].val) B3.template load<W>(a.g, V0, c[3].val);
+            } else {
+                if (c[3].val != P.val) B3.template load<W>(a.g, V1, c[3].val);
+                if (c[2].val != c[3].val) B2.template load<W>(a.g, V1, c[2].val);
+                if (c[1].val != c[2].val) B1.template load<W>(a.g, V1, c[1].val);
+            }
+        };
+        P.val = NO_CELL;
+        const auto grid = [&](int n) { return in_global(scalar_load(a.f + (n - a.f_base))); };
+        TapeEntry c[4], e[4];
+        read(n_hi - 1, c);
+        const char* V0 = grid(n_hi - 1);
+        double hd = scalar_load(a.h + (n_hi - 1 - a.f_base));
+        corners(V0, grid(n_hi), c);
+        read(n_hi - 1 > n_lo ? n_hi - 2 : n_lo, e);
+        for (int n = n_hi - 1; n >= n_lo; --n) {
+            const float h = (float)hd;
+            float G[4][3][3];
+            const auto grad = [&](int s, const GatherCache<DT>& A, const GatherCache<DT>& B, auto mid) {
+                float unused[3], D[3][3];
+                trilerp_grad<decltype(mid)::value>(A.rows(a.g), B.rows(a.g), c[s].f, unused, D);
 #pragma unroll
-                for (int d = 0; d < 3; ++d) sr.x[d] = buf[P3 * (size_t)(n - n0) + d];
-                StageRec rec;
-                if (rk4_step_rec<DT, MODE>(a.g, F(n), F(n + 1), H(n), sr, rec) != S_VALID) {
-                    mismatch = true;
-                    break;
-                }
-                const float h = (float)H(n);
-                const int lv = n - a.f_base;  // grid level of cycle n in the gradient grids
+                for (int r = 0; r < 3; ++r)
 #pragma unroll
-                for (int c = 0; c < NCOT; ++c) {
-                    float lk[4][3], ly[4][3];
+                    for (int d = 0; d < 3; ++d) G[s][r][d] = (float)a.g.inv_sp[r] * D[r][d];
+            };
+            constexpr std::integral_constant<bool, !is_frozen<MODE>> mid{};
+            A1.take(S0, c[1].val);
+            A2.take(A1, c[2].val);
+            if constexpr (is_frozen<MODE>) {
+                B3.take(A2, c[3].val);
+            } else {
+                B3.take(P, c[3].val);
+                B2.take(B3, c[2].val);
+                B1.take(B2, c[1].val);
+            }
+            grad(3, B3, B3, std::false_type{});
+            grad(2, A2, is_frozen<MODE> ? A2 : B2, mid);
+            grad(1, A1, is_frozen<MODE> ? A1 : B1, mid);
+            grad(0, S0, S0, std::false_type{});
+            P = S0;
+            // the step below: its corner values and the entries of the one after it
+            // load while this step's recurrences and sums run
+            const int m1 = n - 1 > n_lo ? n - 1 : n_lo, m2 = n - 2 > n_lo ? n - 2 : n_lo;
+            const char* Vm = grid(m1);
+            hd = scalar_load(a.h + (m1 - a.f_base));
+            corners(Vm, V0, e);
+            V0 = Vm;
+            TapeEntry e2[4];
+            read(m2, e2);
+            const int lv = n - a.f_base;  // grid level of cycle n in the gradient grids
 #pragma unroll
-                    for (int d = 0; d < 3; ++d) lk[3][d] = (h / 6.f) * lam[c][d];
-                    gT(rec.G[3], lk[3], ly[3]);
+            for (int m = 0; m < NCOT; ++m) {
+                float lk[4][3], ly[4][3];
 #pragma unroll
-                    for (int d = 0; d < 3; ++d) lk[2][d] = (h / 3.f) * lam[c][d] + h * ly[3][d];
-                    gT(rec.G[2], lk[2], ly[2]);
+                for (int d = 0; d < 3; ++d) lk[3][d] = (h / 6.f) * lam[m][d];
+                gT(G[3], lk[3], ly[3]);
 #pragma unroll
-                    for (int d = 0; d < 3; ++d) lk[1][d] = (h / 3.f) * lam[c][d] + (0.5f * h) * ly[2][d];
-                    gT(rec.G[1], lk[1], ly[1]);
+                for (int d = 0; d < 3; ++d) lk[2][d] = (h / 3.f) * lam[m][d] + h * ly[3][d];
+                gT(G[2], lk[2], ly[2]);
 #pragma unroll
-                    for (int d = 0; d < 3; ++d) lk[0][d] = (h / 6.f) * lam[c][d] + (0.5f * h) * ly[1][d];
-                    gT(rec.G[0], lk[0], ly[0]);
-                    if (c == 0 && a.grad_f) {
-                        if (is_frozen<MODE>) {
+                for (int d = 0; d < 3; ++d) lk[1][d] = (h / 3.f) * lam[m][d] + (0.5f * h) * ly[2][d];
+                gT(G[1], lk[1], ly[1]);
 #pragma unroll
-                            for (int s = 0; s < 4; ++s) acc_add(a.g, a.grad_f, a.grec, (uint32_t)p, acc, lv, rec.base[s], rec.f[s], 1.f, lk[s]);
-                        } else {
-                            // level n+1 first (it already holds step n+1's share), then level n
-                            acc_add(a.g, a.grad_f, a.grec, (uint32_t)p, acc, lv + 1, rec.base[1], rec.f[1], 0.5f, lk[1]);
-                            acc_add(a.g, a.grad_f, a.grec, (uint32_t)p, acc, lv + 1, rec.base[2], rec.f[2], 0.5f, lk[2]);
-                            acc_add(a.g, a.grad_f, a.grec, (uint32_t)p, acc, lv + 1, rec.base[3], rec.f[3], 1.f, lk[3]);
-                            acc_add(a.g, a.grad_f, a.grec, (uint32_t)p, acc, lv, rec.base[0], rec.f[0], 1.f, lk[0]);
-                            acc_add(a.g, a.grad_f, a.grec, (uint32_t)p, acc, lv, rec.base[1], rec.f[1], 0.5f, lk[1]);
-                            acc_add(a.g, a.grad_f, a.grec, (uint32_t)p, acc, lv, rec.base[2], rec.f[2], 0.5f, lk[2]);
-                        }
+                for (int d = 0; d < 3; ++d) lk[0][d] = (h / 6.f) * lam[m][d] + (0.5f * h) * ly[1][d];
+                gT(G[0], lk[0], ly[0]);
+                if (m == 0 && a.grad_f) {
+                    const auto add = [&](int level, int s, float coef) {
+                        acc_add(a.g, a.grad_f, a.grec, (uint32_t)p, acc, level, c[s], coef, lk[s]);
+                    };
+                    if (is_frozen<MODE>) {
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) add(lv, s, 1.f);
+                    } else {
+                        // level n+1 first (it already holds step n+1's share), then level n
+                        add(lv + 1, 1, 0.5f);
+                        add(lv + 1, 2, 0.5f);
+                        add(lv + 1, 3, 1.f);
+                        add(lv, 0, 1.f);
+                        add(lv, 1, 0.5f);
+                        add(lv, 2, 0.5f);
                     }
-#pragma unroll
-                    for (int d = 0; d < 3; ++d) lam[c][d] += ly[0][d] + ly[1][d] + ly[2][d] + ly[3][d];
                 }
+#pragma unroll
+                for (int d = 0; d < 3; ++d) lam[m][d] += ly[0][d] + ly[1][d] + ly[2][d] + ly[3][d];
             }
-            if (a.grad_f && !mismatch) acc_flush(a.g, a.grad_f, a.grec, (uint32_t)p, acc);  // keep it out of the next recompute
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                c[s] = e[s];
+                e[s] = e2[s];
+            }
         }
+        if (a.grad_f) acc_flush(a.g, a.grad_f, a.grec, (uint32_t)p, acc);
     }
     int drop = prior;
-    if (mismatch) {
-        // no gradient from this seed: its pending sums are dropped and this
-        // call's grid records withdrawn; contributions already in the grids
-        // (added with atomics after its record slots ran out, or by the call
-        // of a later segment) cannot be, and the status says so
-#pragma unroll
-        for (int c = 0; c < NCOT; ++c) lam[c][0] = lam[c][1] = lam[c][2] = 0.f;
+    if (bad) {
+        // no gradient from this seed: this call's grid records are withdrawn;
+        // contributions already in the grids (added with atomics after its
+        // record slots ran out, or by the call of a later segment) cannot be,
+        // and the status says so
         bool withdrawn = true;
         if (a.grad_f) {
             if (a.grec.key) {
@@ -306,13 +363,14 @@ __global__ __launch_bounds__(ADJ_BLOCK) void adjoint_kernel(const AdjointArgs a)
                 for (uint32_t j = 0; j < kept; ++j) a.grec.key[(uint64_t)j * a.grec.P + (uint64_t)p] = unused;
                 withdrawn = acc.nrec <= a.grec.per_seed;
             } else {
-                withdrawn = false;
+                withdrawn = a.sg_first == a.call_first;
             }
-            withdrawn = withdrawn && first;
+            withdrawn = withdrawn && a.call_first == nseg - 1;
         }
         drop = withdrawn ? ADJ_DROPPED : ADJ_DROPPED_PARTIAL;
     }
-    if (a.drop && drop != prior) a.drop[p] = (uint8_t)drop;
+    if (a.drop && (first || drop != prior)) a.drop[p] = (uint8_t)drop;
+    if (a.nrec && !last) a.nrec[p] = acc.nrec;
     if (last) {
         if (a.status_out) a.status_out[p] = (uint8_t)(drop ? drop : status);
 #pragma unroll
@@ -325,6 +383,14 @@ __global__ __launch_bounds__(ADJ_BLOCK) void adjoint_kernel(const AdjointArgs a)
 #pragma unroll
             for (int d = 0; d < 3; ++d) a.lam[(p * NCOT + c) * 3 + d] = lam[c][d];
     }
+}
+
+struct Words {
+    uint64_t v[240];
+};
+
+__global__ void put_words_kernel(uint64_t* dst, const Words w, int n) {
+    if ((int)threadIdx.x < n) dst[threadIdx.x] = w.v[threadIdx.x];
 }
 
 // ---------------------------------------------------------------------------
@@ -372,30 +438,64 @@ __global__ __launch_bounds__(BLOCK) void ftle_kernel(const float* jac, int64_t P
 }
 
 // ---------------------------------------------------------------------------
-template <int DT, int MODE, int NCOT>
-static hipError_t launch_adj_t(const AdjointArgs& a, hipStream_t s) {
-    const int64_t blocks = (a.P + ADJ_BLOCK - 1) / ADJ_BLOCK;
-    hipLaunchKernelGGL((adjoint_kernel<DT, MODE, NCOT>), dim3((unsigned)blocks), dim3(ADJ_BLOCK), 0, s, a);
-    return hipGetLastError();
-}
-
-template <int DT, int MODE>
-static hipError_t launch_adj_m(const AdjointArgs& a, hipStream_t s) {
-    return a.ncot == 1 ? launch_adj_t<DT, MODE, 1>(a, s) : launch_adj_t<DT, MODE, 3>(a, s);
-}
-
-template <int DT>
-static hipError_t launch_adj_d(const AdjointArgs& a, int mode, hipStream_t s) {
-    return mode == MODE_LINEAR ? launch_adj_m<DT, MODE_LINEAR>(a, s) : launch_adj_m<DT, MODE_FROZEN>(a, s);
-}
-
-hipError_t launch_adjoint(const AdjointArgs& a, int dtype, int mode, hipStream_t s) {
-    if (a.P == 0) return hipSuccess;
+template <class F>
+static hipError_t adj_dispatch(int dtype, int mode, F&& f) {
+    auto by_mode = [&](auto dt) {
+        switch (mode) {
+        case MODE_LINEAR: return f(dt, std::integral_constant<int, MODE_LINEAR>{});
+        case MODE_FROZEN: return f(dt, std::integral_constant<int, MODE_FROZEN>{});
+        case MODE_LINEAR | MODE_WIDE: return f(dt, std::integral_constant<int, MODE_LINEAR | MODE_WIDE>{});
+        default: return f(dt, std::integral_constant<int, MODE_FROZEN | MODE_WIDE>{});
+        }
+    };
     switch (dtype) {
-    case DT_F32: return launch_adj_d<DT_F32>(a, mode, s);
-    case DT_F16: return launch_adj_d<DT_F16>(a, mode, s);
-    default: return launch_adj_d<DT_BF16>(a, mode, s);
+    case DT_F32: return by_mode(std::integral_constant<int, DT_F32>{});
+    case DT_F16: return by_mode(std::integral_constant<int, DT_F16>{});
+    default: return by_mode(std::integral_constant<int, DT_BF16>{});
     }
+}
+
+static unsigned adj_blocks(const AdjointArgs& a) { return (unsigned)((a.np + ADJ_BLOCK - 1) / ADJ_BLOCK); }
+
+hipError_t launch_adj_forward(const AdjointArgs& a, int dtype, int mode, hipStream_t s) {
+    return adj_dispatch(dtype, mode, [&](auto dt, auto md) {
+        hipLaunchKernelGGL((adj_forward_kernel<decltype(dt)::value, decltype(md)::value>), dim3(adj_blocks(a)),
+                           dim3(ADJ_BLOCK), 0, s, a);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_adj_recompute(const AdjointArgs& a, int dtype, int mode, hipStream_t s) {
+    return adj_dispatch(dtype, mode, [&](auto dt, auto md) {
+        hipLaunchKernelGGL((adj_recompute_kernel<decltype(dt)::value, decltype(md)::value>),
+                           dim3(adj_blocks(a), (unsigned)(a.sg_first - a.sg_last + 1)), dim3(ADJ_BLOCK), 0, s, a);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_adj_reverse(const AdjointArgs& a, int dtype, int mode, hipStream_t s) {
+    return adj_dispatch(dtype, mode, [&](auto dt, auto md) {
+        if (a.ncot == 1)
+            hipLaunchKernelGGL((adj_reverse_kernel<decltype(dt)::value, decltype(md)::value, 1>), dim3(adj_blocks(a)),
+                               dim3(ADJ_BLOCK), 0, s, a);
+        else
+            hipLaunchKernelGGL((adj_reverse_kernel<decltype(dt)::value, decltype(md)::value, 3>), dim3(adj_blocks(a)),
+                               dim3(ADJ_BLOCK), 0, s, a);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_put_words(uint64_t* dst, const uint64_t* src, size_t n, hipStream_t s) {
+    constexpr size_t M = sizeof(Words) / sizeof(uint64_t);
+    for (size_t k = 0; k < n; k += M) {
+        Words w;
+        const int m = (int)(n - k < M ? n - k : M);
+        for (int i = 0; i < m; ++i) w.v[i] = src[k + i];
+        hipLaunchKernelGGL(put_words_kernel, dim3(1), dim3(256), 0, s, dst + k, w, m);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_ftle(const float* jac, int64_t P, double inv_T, float* out, hipStream_t s) {

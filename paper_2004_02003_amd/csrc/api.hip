@@ -97,6 +97,12 @@ struct bto_ctx {
     std::string err;
 };
 
+// Byte offsets into a grid of at most 4 GiB fit 32 bits.
+static int wide_grids(const bto_ctx* c, int dtype) {
+    const uint64_t bytes = 3ull * c->geom.sz * (uint64_t)c->geom.n[2] * (dtype == BTO_F32 ? 4u : 2u);
+    return bytes > (1ull << 32) ? MODE_WIDE : 0;
+}
+
 static int fail(bto_ctx* c, int code, const char* fmt, ...) {
     if (c) {
         char buf[512];
@@ -698,9 +704,7 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
     if (dtype < BTO_F32 || dtype > BTO_BF16) return fail(c, BTO_EINVAL, "unknown dtype %d", dtype);
     const int tmode = flags & ~(BTO_RECORD_EXIT | BTO_RECORD_CKPT | BTO_SAMPLE_FP64);
     if (tmode != BTO_TIME_LINEAR && tmode != BTO_TIME_FROZEN) return fail(c, BTO_EINVAL, "unknown flags %d", flags);
-    // byte offsets into a grid of at most 4 GiB fit 32 bits
-    const uint64_t grid_bytes = 3ull * c->geom.sz * (uint64_t)c->geom.n[2] * (dtype == BTO_F32 ? 4u : 2u);
-    const int mode = tmode | ((flags & BTO_SAMPLE_FP64) ? MODE_FP64 : 0) | (grid_bytes > (1ull << 32) ? MODE_WIDE : 0);
+    const int mode = tmode | ((flags & BTO_SAMPLE_FP64) ? MODE_FP64 : 0) | wide_grids(c, dtype);
     const int rec = (flags & BTO_RECORD_EXIT) ? 1 : 0;
     const bool rec_ck = (flags & BTO_RECORD_CKPT) != 0;
     for (int32_t q = 0; q <= n_steps; ++q)
@@ -969,10 +973,15 @@ int bto_stats(bto_ctx* c, bto_stats_t* out, void* stream) {
 
 }  // extern "C"
 
-// The adjoint launch over checkpoint segments sg_first .. sg_last with the
-// grids, steps and gradient grids of steps f_base .. f_base + n_local (arguments
-// validated by the callers).  Checkpoints: recomputed into the scratch (whole
-// interval only) or the ones the advection recorded (use_ck).
+// Budget of the adjoint's tape: 64 bytes per step and seed, so 16.7 million
+// steps -- 330,000 seeds over 50 steps in one sweep.
+static constexpr size_t ADJ_TAPE_BYTES = (size_t)1 << 30;
+
+// The adjoint over checkpoint segments sg_first .. sg_last with the grids,
+// steps and gradient grids of steps f_base .. f_base + n_local (arguments
+// validated by the callers).  The tape comes from the adjoint's own forward
+// (whole interval only; through checkpoints in the scratch where the tape does
+// not hold everything) or from the checkpoints the advection recorded (use_ck).
 static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* times, int32_t n_local, int32_t N,
                        int32_t dtype, int mode, bool use_ck, const float* d_cot_end, int32_t n_cot,
                        float* d_grad_seed, float* const* d_grad_fields, uint8_t* d_status, int32_t ckpt_every,
@@ -981,12 +990,35 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
     const int K = ckpt_every < N ? ckpt_every : N;
     const int nseg = (N + K - 1) / K;
     const size_t P = (size_t)c->n_seeds;
-    const size_t tab =
-        ((size_t)(n_local + 1) * 2 * sizeof(void*) + (size_t)n_local * sizeof(double) + 255) & ~(size_t)255;
-    // checkpoint slots live in the scratch unless they were recorded
-    const size_t need = tab + P * 3 * sizeof(double) * ((use_ck ? 0 : (size_t)nseg) + (size_t)K);
+    const size_t nsg = (size_t)(sg_first - sg_last + 1);
+    const size_t words = (size_t)(n_local + 1) * 2 + (size_t)n_local;
+    const size_t tab = (words * sizeof(uint64_t) + 255) & ~(size_t)255;
+    // [tables | records per seed | status | bad | drop | checkpoints, unless they were recorded | tape]
+    const size_t p4 = (P * sizeof(uint32_t) + 255) & ~(size_t)255, p1 = (P + 255) & ~(size_t)255;
+    const size_t ck = use_ck ? 0 : (P * 3 * sizeof(double) * (size_t)nseg + 255) & ~(size_t)255;
+    const size_t fixed = tab + p4 + 3 * p1 + ck;
+    // The tape: as many whole segments as its budget holds, swept in groups; a
+    // single segment beyond it is swept for a part of the seeds at a time.
+    const size_t per = (size_t)K * 4 * sizeof(TapeEntry);
+    size_t np = 0, segs = 0, tape = 0;
+    const auto plan = [&](size_t budget) {
+        np = P;
+        segs = budget / (P * per);
+        if (segs == 0) {
+            np = budget / per / WAVE * WAVE;
+            np = np < (size_t)WAVE ? (size_t)WAVE : np;
+            np = np < P ? np : P;
+            segs = 1;
+        }
+        segs = segs < nsg ? segs : nsg;
+        segs = segs < 32768 ? segs : 32768;
+        const size_t steps = segs * (size_t)K < (size_t)n_local ? segs * (size_t)K : (size_t)n_local;
+        tape = np * steps * 4 * sizeof(TapeEntry);
+    };
     hipError_t e;
-    if (need > c->adj_bytes) {
+    size_t budget = ADJ_TAPE_BYTES;
+    plan(budget);
+    if (fixed + tape > c->adj_bytes) {
         if (c->adj_scratch) {
             e = hipStreamSynchronize(s);
             if (e != hipSuccess) return hip_fail(c, e, "adjoint scratch sync");
@@ -994,25 +1026,28 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
             c->adj_scratch = nullptr;
             c->adj_bytes = 0;
         }
-        if (hipMalloc(&c->adj_scratch, need) != hipSuccess) {
+        // a card without that much memory left gets by with a shorter tape
+        while (hipMalloc(&c->adj_scratch, fixed + tape) != hipSuccess) {
             (void)hipGetLastError();
-            return fail(c, BTO_ENOMEM, "adjoint scratch of %zu bytes", need);
+            c->adj_scratch = nullptr;
+            const size_t had = tape;
+            while (budget > 0 && tape == had) plan(budget /= 2);
+            if (tape == had) return fail(c, BTO_ENOMEM, "adjoint scratch of %zu bytes", fixed + tape);
         }
-        c->adj_bytes = need;
+        c->adj_bytes = fixed + tape;
     }
     char* base = static_cast<char*>(c->adj_scratch);
-    std::vector<char> host(tab, 0);
-    const void** hf = reinterpret_cast<const void**>(host.data());
-    void** hg = reinterpret_cast<void**>(host.data() + (size_t)(n_local + 1) * sizeof(void*));
-    double* hh = reinterpret_cast<double*>(host.data() + (size_t)(n_local + 1) * 2 * sizeof(void*));
+    std::vector<uint64_t> host(words);
     for (int32_t q = 0; q <= n_local; ++q) {
-        hf[q] = d_fields[q];
-        hg[q] = d_grad_fields ? (void*)d_grad_fields[q] : nullptr;
+        host[q] = (uint64_t)(uintptr_t)d_fields[q];
+        host[n_local + 1 + q] = d_grad_fields ? (uint64_t)(uintptr_t)d_grad_fields[q] : 0;
     }
-    for (int32_t q = 0; q < n_local; ++q) hh[q] = times[q + 1] - times[q];
-    e = hipMemcpyAsync(base, host.data(), tab, hipMemcpyHostToDevice, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return hip_fail(c, e, "adjoint tables upload");
+    for (int32_t q = 0; q < n_local; ++q) {
+        const double h = times[q + 1] - times[q];
+        std::memcpy(&host[2 * (size_t)(n_local + 1) + q], &h, sizeof(h));
+    }
+    e = launch_put_words(reinterpret_cast<uint64_t*>(base), host.data(), words, s);
+    if (e != hipSuccess) return hip_fail(c, e, "adjoint tables");
     AdjointArgs a{};
     a.f = reinterpret_cast<const char* const*>(base);
     a.grad_f = d_grad_fields ? reinterpret_cast<float* const*>(base + (size_t)(n_local + 1) * sizeof(void*)) : nullptr;
@@ -1029,23 +1064,21 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
     }
     a.cot = d_cot_end;
     a.grad_seed = d_grad_seed;
-    if (use_ck) {
-        a.ckpt = c->ck_rec;
-        a.ck_stride = c->cap * 3;
-        a.buf = reinterpret_cast<double*>(base + tab);
-        a.rec_meta = c->rec_meta;
-    } else {
-        a.ckpt = reinterpret_cast<double*>(base + tab);
-        a.ck_stride = (int64_t)P * 3;
-        a.buf = a.ckpt + P * 3 * (size_t)nseg;
-        a.rec_meta = nullptr;
-    }
+    uint32_t* nrec = reinterpret_cast<uint32_t*>(base + tab);
+    a.status = reinterpret_cast<uint8_t*>(base + tab + p4);
+    a.bad = a.status + p1;
+    a.ckpt = use_ck ? c->ck_rec : reinterpret_cast<double*>(a.status + 3 * p1);
+    a.ck_stride = use_ck ? c->cap * 3 : (int64_t)P * 3;
+    a.rec_meta = use_ck ? c->rec_meta : nullptr;
+    a.tape = reinterpret_cast<TapeEntry*>(base + fixed);
     a.status_out = d_status;
-    a.sg_first = sg_first;
-    a.sg_last = sg_last;
     a.f_base = f_base;
-    a.lam = lam;
-    a.drop = drop;
+    a.call_first = sg_first;
+    // carried from one launch to the next: by the caller of a segment, or, between
+    // the groups of a call, in the gradients it returns
+    a.lam = lam ? lam : d_grad_seed;
+    a.drop = drop ? drop : a.bad + p1;
+    if (np < P || segs < nsg) a.nrec = nrec;
     // grid gradients: records for the sorted reduction, unless the key does not fit
     a.grec = GradRec{};
     uint64_t* key_out = nullptr;
@@ -1114,8 +1147,31 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
             }
         }
     }
-    e = launch_adjoint(a, dtype, mode, s);
-    if (e != hipSuccess) return hip_fail(c, e, "adjoint launch");
+    const int md = mode | wide_grids(c, dtype);
+    // the interval's own forward: straight onto the tape where it holds everything
+    const bool whole = np == P && segs == nsg;
+    if (!use_ck) {
+        AdjointArgs w = a;
+        w.p0 = 0;
+        w.np = (int64_t)P;
+        if (whole) w.ckpt = nullptr;
+        else w.tape = nullptr;
+        e = launch_adj_forward(w, dtype, md, s);
+    } else {
+        e = launch_tile_fill(reinterpret_cast<uint32_t*>(a.bad), p1 / sizeof(uint32_t), s);
+    }
+    if (e != hipSuccess) return hip_fail(c, e, "adjoint forward");
+    for (size_t p0 = 0; p0 < P; p0 += np) {
+        a.p0 = (int64_t)p0;
+        a.np = (int64_t)(P - p0 < np ? P - p0 : np);
+        for (int sg = sg_first; sg >= sg_last; sg -= (int)segs) {
+            a.sg_first = sg;
+            a.sg_last = sg - (int)segs + 1 < sg_last ? sg_last : sg - (int)segs + 1;
+            if (use_ck || !whole) e = launch_adj_recompute(a, dtype, md, s);
+            if (e == hipSuccess) e = launch_adj_reverse(a, dtype, md, s);
+            if (e != hipSuccess) return hip_fail(c, e, "adjoint launch");
+        }
+    }
     if (a.grec.key) {
         e = launch_grad_reduce(a.grec, n_slots, key_out, idx_out, bounds, sort_temp, sort_bytes, a.grad_f, c->geom, s);
         if (e != hipSuccess) return hip_fail(c, e, "gradient reduction");
@@ -1226,10 +1282,6 @@ int bto_adjoint_segment(bto_ctx* c, int32_t segment, const void* const* d_fields
     }
     float* lam = static_cast<float*>(c->seg_buf);
     uint8_t* drop = reinterpret_cast<uint8_t*>(static_cast<char*>(c->seg_buf) + lam_bytes);
-    if (first) {
-        hipError_t e = launch_tile_fill(reinterpret_cast<uint32_t*>(drop), ((size_t)c->n_seeds + 3) / 4, s);
-        if (e != hipSuccess) return hip_fail(c, e, "segment state clear");
-    }
     rc = adjoint_run(c, d_fields, times, nl, N, dtype, mode, true, d_cot_end, n_cot, d_grad_seed, d_grad_fields,
                      d_status, c->ck_k, segment, segment, n0, lam, drop, s);
     if (rc) return rc;

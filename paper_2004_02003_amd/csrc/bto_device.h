@@ -323,6 +323,16 @@ struct GatherCache {
             W[r][3] = q.w;
         }
     }
+    // This lane's cell from another cache where it is the same one.
+    __device__ __forceinline__ void take(const GatherCache& o, uint32_t b) {
+        const bool same = o.val == b;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) W[r][j] = same ? o.W[r][j] : W[r][j];
+        sel3 = same ? o.sel3 : sel3;
+        val = b;
+    }
     __device__ __forceinline__ Rows16<DT> rows(const Geom& g) const {
         // The shift and the selector are made opaque: otherwise the compiler
         // sees that a cell kept from one stage to the next decodes to the same
@@ -357,6 +367,14 @@ struct GatherCache<DT_F32> {
 #pragma unroll
             for (int q = 0; q < 6; ++q) R[r][q] = x.v[q];
         }
+    }
+    __device__ __forceinline__ void take(const GatherCache& o, uint32_t b) {
+        const bool same = o.val == b;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+            for (int q = 0; q < 6; ++q) R[r][q] = same ? o.R[r][q] : R[r][q];
+        val = b;
     }
     __device__ __forceinline__ const GatherCache& rows(const Geom&) const { return *this; }
 };
@@ -650,20 +668,6 @@ __device__ __forceinline__ bool finite3(const R k[3]) {
     return __builtin_isfinite(k[0]) && __builtin_isfinite(k[1]) && __builtin_isfinite(k[2]);
 }
 
-// Per-lane stepping state: FP64 position plus the two cached levels.
-template <int DT>
-struct Stepper {
-    double x[3];
-    CellCache<DT> A;  // level n   (cycle of the step's start)
-    CellCache<DT> B;  // level n+1
-};
-
-template <int DT>
-__device__ __forceinline__ void stepper_init(Stepper<DT>& st) {
-    st.A.base = NO_CELL;
-    st.B.base = NO_CELL;
-}
-
 // One classic RK4 step of one cycle: stage times t, t+h/2, t+h/2, t+h with the
 // field linear in time between V0 (cycle n) and V1 (cycle n+1), or V0 only
 // when frozen.  Each stage velocity is checked finite right after sampling;
@@ -779,6 +783,11 @@ __device__ __forceinline__ int rk4_step(const Geom& g, const char* V0, const cha
     return S_VALID;
 }
 
+struct NoStage {
+    template <class C>
+    __device__ __forceinline__ void operator()(int, const C&) const {}
+};
+
 // Wait for every load issued so far.
 __device__ __forceinline__ void wait_loads() {
     __builtin_amdgcn_sched_barrier(0);
@@ -825,13 +834,14 @@ __device__ __forceinline__ bool inside_flat(const Geom& g, const double p[3]) {
 //     conversions of f16 values folded into the FMAs (tile_gather_kernel, f16:
 //     1,411 vector instructions and 127 registers before, 982 and 91 now).
 // On entry A holds a cell of level n (or NO_CELL), B nothing; x is inside.
+// on_stage(s, c) is given the cell and the offsets that stage s samples.
 // one_by_one (uniform): wait for level n before level n + 1 is asked for, as
 // rk4_step does -- two round trips, but half the lines in flight, which is the
 // better where the wavefronts' lines no longer fit the L1 (see the callers).
-template <int DT, int MODE, class OnExit>
+template <int DT, int MODE, class OnExit, class OnStage = NoStage>
 __device__ __forceinline__ int rk4_step_gather(const Geom& g, const char* V0, const char* V1, const StepSizes& hs,
                                                double* x, GatherCache<DT>& A, GatherCache<DT>& B, bool one_by_one,
-                                               OnExit&& on_exit) {
+                                               OnExit&& on_exit, OnStage&& on_stage = OnStage{}) {
     using R = SampleT<MODE>;
     constexpr bool W = is_wide<MODE>;
     int status = S_VALID;
@@ -856,6 +866,7 @@ __device__ __forceinline__ int rk4_step_gather(const Geom& g, const char* V0, co
     // of the other level once from each)
     GatherCell<R> c = locate_clamped<R>(g, x);
     uint32_t b = opaque(c.val);
+    on_stage(0, c);
     if (A.val != c.val) A.template load<W>(g, V0, b);
     trilerp(A.rows(g), c.f, k);
 #pragma unroll
@@ -864,6 +875,7 @@ __device__ __forceinline__ int rk4_step_gather(const Geom& g, const char* V0, co
 
     c = locate_clamped<R>(g, y);
     b = opaque(c.val);
+    on_stage(1, c);
     if (A.val != c.val) A.template load<W>(g, V0, b);
     if constexpr (!is_frozen<MODE>) {
         if (one_by_one) wait_loads();
@@ -878,6 +890,7 @@ __device__ __forceinline__ int rk4_step_gather(const Geom& g, const char* V0, co
 
     c = locate_clamped<R>(g, y);
     b = opaque(c.val);
+    on_stage(2, c);
     if (A.val != c.val) {
         A.template load<W>(g, V0, b);
         if constexpr (!is_frozen<MODE>) {
@@ -896,6 +909,7 @@ __device__ __forceinline__ int rk4_step_gather(const Geom& g, const char* V0, co
 
     c = locate_clamped<R>(g, y);
     b = opaque(c.val);
+    on_stage(3, c);
     if constexpr (!is_frozen<MODE>) {
         if (B.val != c.val) B.template load<W>(g, V1, b);
         trilerp(B.rows(g), c.f, k);
@@ -909,25 +923,6 @@ __device__ __forceinline__ int rk4_step_gather(const Geom& g, const char* V0, co
     point(hs.sixth, ks);
 #pragma unroll
     for (int d = 0; d < 3; ++d) x[d] = status == S_VALID ? y[d] : x[d];
-    return status;
-}
-
-// Stepping with two cache slots whose roles alternate: step s reads level n
-// from slot s % 2 and level n+1 from the other slot, which then holds the
-// next step's level n, so no corner values are ever copied.
-template <int DT, int MODE>
-__device__ __forceinline__ int rk4_step_alt(const Geom& g, const char* V0, const char* V1, double h, int s,
-                                            Stepper<DT>& st) {
-    int status;
-    const auto no_exit = [](const double*) {};
-    if ((s & 1) == 0) {
-        status = rk4_step<DT, MODE>(g, V0, V1, h, st.x, st.A, st.B, no_exit);
-        if (!is_frozen<MODE>) st.A.base = NO_CELL;  // will receive level n+2
-    } else {
-        status = rk4_step<DT, MODE>(g, V0, V1, h, st.x, st.B, st.A, no_exit);
-        if (!is_frozen<MODE>) st.B.base = NO_CELL;
-    }
-    if (is_frozen<MODE>) st.A.base = st.B.base = NO_CELL;
     return status;
 }
 

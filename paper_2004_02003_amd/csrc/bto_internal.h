@@ -44,6 +44,18 @@ __device__ __forceinline__ double uniform(double v) {
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
+// Sixteen bytes as four registers (a struct's array is kept in memory where it
+// crosses a branch).
+typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+
+// A table entry read through the scalar cache (constant during the launch, the
+// same for the whole wavefront).
+template <class T>
+__device__ __forceinline__ T scalar_load(const T* p) {
+    using C = const __attribute__((address_space(4))) T*;
+    return *(C)(uintptr_t)p;
+}
+
 struct Segs {
     int64_t base[NSEG];  // first slot of each segment
 };
@@ -137,33 +149,47 @@ struct GradRec {
     int32_t cell_bits, level_bits;
 };
 
+// The adjoint's tape: what the reverse sweep needs of a step, one 16-byte entry
+// per stage -- the value index of the cell sampled and the three FP32 offsets
+// in it -- at [step][stage][seed], so a wavefront's 64 entries are one
+// contiguous kilobyte.
+struct TapeEntry {
+    uint32_t val;
+    float f[3];
+};
+
 struct AdjointArgs {
-    const char* const* f;       // device array: N + 1 grids
-    const double* h;            // device array: N step sizes
+    const char* const* f;       // device array: grids of the call's cycles
+    const double* h;            // device array: its step sizes
     Geom g;
     int32_t N;                  // steps
     int32_t k;                  // checkpoint every k steps
     int32_t ncot;               // cotangent vectors per seed (1 or 3)
-    int64_t P;
+    int64_t P;                  // seeds
+    int64_t p0, np;             // the seeds of this launch: p0 .. p0 + np - 1
     const double* seed_xyz;     // P x 3 world
     double origin[3], sp[3];
     const float* cot;           // P x ncot x 3, d L / d x_end (world)
     float* grad_seed;           // P x ncot x 3, d L / d x_0 (world)
-    float* const* grad_f;       // device array of N + 1 FP32 grids (accumulated) or null
-    double* ckpt;               // ceil(N/k) slots of ck_stride doubles ([slot][seed][xyz], cell units)
+    float* const* grad_f;       // device array of FP32 grids (accumulated) or null
+    double* ckpt;               // ceil(N/k) slots of ck_stride doubles ([slot][seed][xyz], cell units), or null
     int64_t ck_stride;          // doubles per checkpoint slot (>= 3 P)
-    double* buf;                // k x P x 3 scratch (slot-major)
-    uint8_t* status_out;        // P (may be null): status of the recomputed forward
+    TapeEntry* tape;            // steps of segments sg_last .. sg_first, np seeds each (null: forward without a tape)
+    uint8_t* status;            // P: status of the adjoint's own forward (rec_meta null)
+    uint8_t* bad;               // P: a recomputed step contradicted the forward
+    uint8_t* status_out;        // P (may be null): reported status
     const int32_t* rec_meta;    // non-null: take the forward from recorded checkpoints and these records
     GradRec grec;               // grid-gradient records (grec.key null: atomics)
-    // Segments swept by this launch, sg_first down to sg_last (the whole
-    // interval: nseg - 1 .. 0).  f, h and grad_f hold the grids, steps and
-    // gradient grids from step f_base on.  lam (P x ncot x 3, cell units)
-    // carries the cotangents from one launch to the next (read unless sg_first
-    // is the last segment, written unless sg_last is 0); drop (P bytes, may be
-    // null for a single launch) marks seeds dropped by an earlier launch.
+    uint32_t* nrec;             // P: records written by each seed so far in this call (null: one launch does all)
+    // Segments of this launch, sg_first down to sg_last (the whole interval:
+    // nseg - 1 .. 0).  f, h and grad_f hold the grids, steps and gradient grids
+    // from step f_base on.  lam (P x ncot x 3, cell units) carries the
+    // cotangents from one launch to the next (read unless sg_first is the last
+    // segment, written unless sg_last is 0); drop (P bytes, may be null where
+    // one launch does all) marks seeds dropped by an earlier launch.
     int32_t sg_first, sg_last;
     int32_t f_base;
+    int32_t call_first;         // first segment of this call
     float* lam;
     uint8_t* drop;
 };
@@ -354,7 +380,16 @@ hipError_t launch_touch_step(const TouchArgs& a, int dtype, int mode, hipStream_
 hipError_t launch_touch_count(uint32_t* bits, size_t words, unsigned long long* out, hipStream_t s);
 hipError_t launch_touch_zero(unsigned long long* p, size_t n, hipStream_t s);
 int advect_max_blocks_per_cu(int dtype, int mode, int lanes_per_particle, int record_exit);
-hipError_t launch_adjoint(const AdjointArgs& a, int dtype, int mode, hipStream_t s);
+// The adjoint's launches, for the seeds p0 .. p0 + np - 1: its own forward from
+// the seeds (tape and checkpoints where given); the tape of segments sg_last ..
+// sg_first from their checkpoints, all segments at once; the reverse sweep
+// over them.  mode: MODE_WIDE set for grids beyond 4 GiB.
+hipError_t launch_adj_forward(const AdjointArgs& a, int dtype, int mode, hipStream_t s);
+hipError_t launch_adj_recompute(const AdjointArgs& a, int dtype, int mode, hipStream_t s);
+hipError_t launch_adj_reverse(const AdjointArgs& a, int dtype, int mode, hipStream_t s);
+// n 64-bit words from the host into device memory, as kernel arguments (no
+// copy whose source would have to outlive the call).
+hipError_t launch_put_words(uint64_t* dst, const uint64_t* src, size_t n, hipStream_t s);
 size_t grad_sort_temp_bytes(uint64_t n, int bits);
 // Mark all n record slots unused (before the adjoint sweep writes them).
 hipError_t launch_grad_clear(const GradRec& r, uint64_t n, hipStream_t s);

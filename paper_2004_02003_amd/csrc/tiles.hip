@@ -280,18 +280,6 @@ struct StageRegs {
     }
 };
 
-// A particle state as four registers (the compiler keeps the struct's array in
-// memory where it crosses a branch).
-typedef uint32_t U4 __attribute__((ext_vector_type(4)));
-
-// A table entry read through the scalar cache (constant during the launch, the
-// same for the whole wavefront).
-template <class T>
-__device__ __forceinline__ T scalar_load(const T* p) {
-    using C = const __attribute__((address_space(4))) T*;
-    return *(C)(uintptr_t)p;
-}
-
 __device__ __forceinline__ void unpack_tile(int32_t t, int tc[3]) {
     tc[0] = t & 1023;
     tc[1] = (t >> 10) & 1023;

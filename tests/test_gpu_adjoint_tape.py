@@ -1,0 +1,62 @@
+"""The adjoint's tape (1 GiB, 64 bytes per step and seed): an interval that
+passes it is swept in groups of checkpoint segments, a single segment that
+passes it in parts of the seeds.  Both give the gradients of seed sets that
+fit, recomputed or recorded."""
+
+import sys
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.skip("no HIP device")
+    from paper_2004_02003_amd import _lib
+
+    _lib.load()
+
+
+def _grads(n, grids, times, seeds, cot, ckpt, recorded, grid_grad=False):
+    from paper_2004_02003_amd import Context
+
+    with Context(n, len(seeds)) as ctx:
+        ctx.set_tuning(ckpt_every=ckpt)
+        ctx.seed_explicit(seeds)
+        if recorded:
+            ctx.advect(grids, times, record_ckpt=True)
+        gg = [torch.zeros(g.shape, dtype=torch.float32, device="cuda") for g in grids] if grid_grad else None
+        st = torch.empty(len(seeds), dtype=torch.uint8, device="cuda")
+        out = ctx.adjoint(grids, times, cot, grad_grids=gg, ckpt_every=ckpt, status=st, recorded=recorded)
+        torch.cuda.synchronize()
+    return out.cpu(), st.cpu(), None if gg is None else torch.stack(gg).cpu()
+
+
+# 360,000 seeds x 50 steps: 1.07 GiB of tape; ckpt 10: groups of 4 + 1
+# segments, ckpt 50: one segment, 335,544 seeds and the rest
+@pytest.mark.parametrize("dtype,recorded", [(torch.float32, False), (torch.float16, True)])
+def test_intervals_beyond_the_tape(dtype, recorded):
+    n, N, P = (27, 22, 17), 50, 360_000
+    g = torch.Generator(device="cuda").manual_seed(7)
+    grids = [(0.3 * torch.randn((n[2], n[1], n[0], 3), device="cuda", generator=g)).to(dtype) for _ in range(N + 1)]
+    times = np.arange(N + 1) * 0.1
+    hi = torch.tensor([v - 1.0 for v in n], dtype=torch.float64, device="cuda")
+    seeds = torch.rand((P, 3), dtype=torch.float64, device="cuda", generator=g) * hi
+    cot = 0.5 + torch.rand((P, 1, 3), device="cuda", generator=g)  # one sign: no cancelled sums
+    print(f"[gpu-case] tape {dtype} recorded={recorded}", file=sys.stderr, flush=True)
+    runs = {k: _grads(n, grids, times, seeds, cot, k, recorded, True) for k in (10, 50)}
+    for k, (a, sa, _) in runs.items():
+        assert 0.3 * P < int((sa == 0).sum()) < P
+        for lo, m in ((0, 777), (335_000, 1500), (P - 65, 65)):
+            s, ss, _ = _grads(n, grids, times, seeds[lo:lo + m].contiguous(), cot[lo:lo + m].contiguous(), k, recorded)
+            assert torch.equal(ss, sa[lo:lo + m]) and torch.equal(s, a[lo:lo + m]), (k, lo, m)
+    if not recorded:  # (a recorded forward is rounded at its launches, which the spacing cuts)
+        (a, sa, ga), (b, sb, gb) = runs[10], runs[50]
+        assert torch.equal(sa, sb) and torch.equal(a, b)
+        # about 50 seeds per cell and level: each grid sum has fewer than 2,000
+        # terms of one sign up to the flow's shear, added in different groupings
+        assert (ga - gb).abs().max() <= 2e-5 * ga.abs().max()
