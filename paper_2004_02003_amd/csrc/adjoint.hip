@@ -61,6 +61,11 @@ struct GradAcc {
     float v[8][3];
 };
 
+__device__ __forceinline__ void put_key(const GradRec& R, uint64_t slot, uint64_t key) {
+    if (R.key_bytes == 4) static_cast<uint32_t*>(R.key)[slot] = (uint32_t)key;
+    else static_cast<uint64_t*>(R.key)[slot] = key;
+}
+
 __device__ __forceinline__ void acc_flush(const Geom& g, float* const* gf, const GradRec& R, uint32_t pid,
                                           GradAcc& A) {
     if (A.val == NO_CELL) return;
@@ -71,8 +76,9 @@ __device__ __forceinline__ void acc_flush(const Geom& g, float* const* gf, const
         const uint32_t base = A.val / 3u;
         const uint32_t i = base % g.sy, j = (base / g.sy) % (uint32_t)g.n[1], k = base / g.sz;
         const uint64_t colour = (uint64_t)((i & 1u) | ((j & 1u) << 1) | ((k & 1u) << 2));
-        R.key[slot] = (colour << (R.level_bits + R.cell_bits)) | ((uint64_t)A.level << R.cell_bits) |
-                      (uint64_t)base;  // the slot's sort value, its index, was written by the clear
+        const uint64_t key = (colour << (R.level_bits + R.cell_bits)) | ((uint64_t)A.level << R.cell_bits) |
+                             (uint64_t)base;
+        put_key(R, slot, key);
         float4* out = reinterpret_cast<float4*>(R.val + 24 * (size_t)slot);
 #pragma unroll
         for (int q = 0; q < 6; ++q)
@@ -359,8 +365,8 @@ __global__ __launch_bounds__(ADJ_BLOCK) void adj_reverse_kernel(const AdjointArg
         if (a.grad_f) {
             if (a.grec.key) {
                 const uint32_t kept = acc.nrec < a.grec.per_seed ? acc.nrec : a.grec.per_seed;
-                const uint64_t unused = (uint64_t)8 << (a.grec.level_bits + a.grec.cell_bits);  // colour 8
-                for (uint32_t j = 0; j < kept; ++j) a.grec.key[(uint64_t)j * a.grec.P + (uint64_t)p] = unused;
+                const uint64_t unused = 1ull << (a.grec.level_bits + a.grec.cell_bits + 3);
+                for (uint32_t j = 0; j < kept; ++j) put_key(a.grec, (uint64_t)j * a.grec.P + (uint64_t)p, unused);
                 withdrawn = acc.nrec <= a.grec.per_seed;
             } else {
                 withdrawn = a.sg_first == a.call_first;

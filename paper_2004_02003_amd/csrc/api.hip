@@ -1081,11 +1081,7 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
     if (np < P || segs < nsg) a.nrec = nrec;
     // grid gradients: records for the sorted reduction, unless the key does not fit
     a.grec = GradRec{};
-    uint64_t* key_out = nullptr;
-    uint32_t* idx_out = nullptr;
-    uint32_t* bounds = nullptr;
-    void* sort_temp = nullptr;
-    size_t sort_bytes = 0;
+    GradSort sort{};
     uint64_t n_slots = 0;
     bool grads_distinct = true;  // the colour passes store without atomics: one buffer per grid
     if (d_grad_fields) {
@@ -1105,6 +1101,7 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
         r.cell_bits = bits_for(npts - 1);
         r.level_bits = bits_for((uint64_t)n_local);
         const int kb = r.cell_bits + r.level_bits + 3;
+        r.key_bytes = kb + 1 <= 32 ? 4 : 8;
         const uint64_t per = 2 * sizeof(uint64_t) + 2 * sizeof(uint32_t) + 24 * sizeof(float);
         const uint64_t max_slots = ((uint64_t)4 << 30) / per;  // at most ~4 GiB of records
         // about one flush per seed and level when particles keep their cells, plus cell changes
@@ -1113,8 +1110,7 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
         if (kb + 1 <= 64 && ps >= 1) {
             r.per_seed = (uint32_t)ps;
             n_slots = ((uint64_t)P * ps + 15) & ~(uint64_t)15;  // keeps every array 128-byte aligned
-            sort_bytes = grad_sort_temp_bytes(n_slots, kb + 1);
-            const size_t temp_r = (sort_bytes + 255) & ~(size_t)255;
+            const size_t temp_r = (radix_temp_bytes(n_slots) + 255) & ~(size_t)255;
             const size_t need_r = temp_r + (size_t)n_slots * per + 256;
             if (need_r > c->grec_bytes) {
                 if (c->grec_buf) {
@@ -1131,16 +1127,17 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
                     c->grec_bytes = need_r;
                 }
             }
-            if (c->grec_buf && sort_bytes > 0) {
-                // [sort temp | keys | sorted keys | indices | sorted indices | values | colour bounds]
+            if (c->grec_buf) {
+                // [sort temp | keys | sorted keys | slots x 2 | values | colour bounds]
                 char* q = static_cast<char*>(c->grec_buf);
-                sort_temp = q;
-                r.key = reinterpret_cast<uint64_t*>(q + temp_r);
-                key_out = r.key + n_slots;
-                r.idx = reinterpret_cast<uint32_t*>(key_out + n_slots);
-                idx_out = r.idx + n_slots;
-                r.val = reinterpret_cast<float*>(idx_out + n_slots);
-                bounds = reinterpret_cast<uint32_t*>(r.val + 24 * (size_t)n_slots);
+                sort.temp = q;
+                r.key = q + temp_r;
+                sort.key_alt = static_cast<char*>(r.key) + n_slots * (size_t)r.key_bytes;
+                sort.idx[0] = reinterpret_cast<uint32_t*>(static_cast<char*>(sort.key_alt) +
+                                                          n_slots * (size_t)r.key_bytes);
+                sort.idx[1] = sort.idx[0] + n_slots;
+                r.val = reinterpret_cast<float*>(sort.idx[1] + n_slots);
+                sort.bounds = reinterpret_cast<uint32_t*>(r.val + 24 * (size_t)n_slots);
                 e = launch_grad_clear(r, n_slots, s);
                 if (e != hipSuccess) return hip_fail(c, e, "gradient record clear");
                 a.grec = r;
@@ -1173,7 +1170,7 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
         }
     }
     if (a.grec.key) {
-        e = launch_grad_reduce(a.grec, n_slots, key_out, idx_out, bounds, sort_temp, sort_bytes, a.grad_f, c->geom, s);
+        e = launch_grad_reduce(a.grec, sort, n_slots, a.grad_f, c->geom, s);
         if (e != hipSuccess) return hip_fail(c, e, "gradient reduction");
     }
     return BTO_OK;

@@ -141,8 +141,8 @@ struct FlowmapArgs {
 // timing.  A seed's flushes beyond per_seed fall back to atomics.  key == null:
 // atomics.
 struct GradRec {
-    uint64_t* key;
-    uint32_t* idx;              // record index (the sort's values)
+    void* key;                  // uint32_t (key_bytes 4) or uint64_t per slot; null: atomics
+    int32_t key_bytes;
     float* val;                 // per_seed * P x 24 floats
     uint32_t per_seed;
     uint32_t P;
@@ -390,25 +390,34 @@ hipError_t launch_adj_reverse(const AdjointArgs& a, int dtype, int mode, hipStre
 // n 64-bit words from the host into device memory, as kernel arguments (no
 // copy whose source would have to outlive the call).
 hipError_t launch_put_words(uint64_t* dst, const uint64_t* src, size_t n, hipStream_t s);
-size_t grad_sort_temp_bytes(uint64_t n, int bits);
 // Mark all n record slots unused (before the adjoint sweep writes them).
 hipError_t launch_grad_clear(const GradRec& r, uint64_t n, hipStream_t s);
+// Scratch of the reduction: the sort's second key array, its two index arrays,
+// nine colour bounds and a pair count, and radix_temp_bytes(n) of temp.
+struct GradSort {
+    void* key_alt;
+    uint32_t* idx[2];
+    uint32_t* bounds;
+    void* temp;
+};
 // Sort the n record slots by key and add each (level, cell) group's sum to the
 // grids, one parity colour at a time (no two cells of one colour share a corner).
-hipError_t launch_grad_reduce(const GradRec& r, uint64_t n, uint64_t* key_out, uint32_t* idx_out, uint32_t* bounds,
-                              void* temp, size_t temp_bytes, float* const* gf, const Geom& g, hipStream_t s);
+hipError_t launch_grad_reduce(const GradRec& r, const GradSort& w, uint64_t n, float* const* gf, const Geom& g,
+                              hipStream_t s);
 hipError_t launch_ftle(const float* jac, int64_t P, double inv_T, float* out, hipStream_t s);
 size_t rebin_temp_bytes(int64_t nbins_total);
 
-// Device-wide exclusive scan of n counts (in != out; temp: scan_temp_bytes)
-// and stable LSD radix sort of (key, value) pairs on the low `bits` key bits,
-// ping-ponging between (key, val) and (key_alt, val_alt); *result_in_alt says
-// which pair of arrays holds the sorted result (temp: radix_temp_bytes).
+// Device-wide exclusive scan of n counts (in != out; temp: scan_temp_bytes).
 size_t scan_temp_bytes(uint64_t n);
 hipError_t launch_exclusive_scan(const uint32_t* in, uint32_t* out, uint64_t n, void* temp, hipStream_t s);
+// Stable LSD radix sort of the slots 0 .. n - 1 by the low `bits` bits of their
+// keys; slots whose bit `bits` is set are left out.  The sorted keys and slot
+// numbers end in (key, idx0) or (key_alt, idx1), as *result_in_alt says, their
+// number in *count (device); temp: radix_temp_bytes.  key_bytes: 4 or 8.
 size_t radix_temp_bytes(uint64_t n);
-hipError_t launch_radix_sort_pairs(uint64_t* key, uint32_t* val, uint64_t* key_alt, uint32_t* val_alt, uint64_t n,
-                                   int bits, void* temp, bool* result_in_alt, hipStream_t s);
+hipError_t launch_radix_sort_slots(void* key, void* key_alt, uint32_t* idx0, uint32_t* idx1, int key_bytes,
+                                   uint64_t n, int bits, uint32_t* count, void* temp, bool* result_in_alt,
+                                   hipStream_t s);
 hipError_t launch_rebin(const RebinArgs& a, hipStream_t s);
 
 }  // namespace bto

@@ -3,8 +3,7 @@
 // The reverse sweep writes one record per accumulator flush into a slot fixed
 // by (flush rank, seed): the 8 corner gradients (x 3 components) of one cell
 // of one grid level, keyed by parity colour | level | cell (unused slots carry
-// a key above every colour).  A stable radix sort (radix.hip) orders the
-// records by key;
+// the bit above).  A stable radix sort (radix.hip) orders the records by key;
 // then, one colour at a time (a contiguous range of the sorted keys), each
 // (level, cell) group is summed in slot order (the flush's rank, then the
 // seed id) and added to the grid's 8 corners with plain loads and stores.
@@ -18,71 +17,85 @@
 
 namespace bto {
 
-// Before a sweep: every slot unused, and each slot's sort value its own index
-// (written here in one coalesced pass rather than by the sweep's scattered
-// record stores).
-__global__ __launch_bounds__(BLOCK) void grad_clear_kernel(uint64_t* key, uint32_t* idx, uint64_t n, uint64_t empty) {
-    for (uint64_t i = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; i < n; i += (uint64_t)gridDim.x * BLOCK) {
+// Before a sweep: every slot unused.
+template <class K>
+__global__ __launch_bounds__(BLOCK) void grad_clear_kernel(K* key, uint64_t n, K empty) {
+    for (uint64_t i = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; i < n; i += (uint64_t)gridDim.x * BLOCK)
         key[i] = empty;
-        idx[i] = (uint32_t)i;
+}
+
+// bounds[c] = first sorted record of colour c (c = 0..8; bounds[8]: their
+// number, found by the sort in bounds[9]).
+template <class K>
+__global__ __launch_bounds__(BLOCK) void grad_bounds_kernel(const K* key, int colour_shift, uint32_t* bounds) {
+    const uint32_t n = bounds[9];
+    for (uint32_t i = blockIdx.x * BLOCK + threadIdx.x; i <= n; i += gridDim.x * BLOCK) {
+        const uint32_t c = i < n ? (uint32_t)(key[i] >> colour_shift) : 8u;
+        const uint32_t lo = i > 0 ? (uint32_t)(key[i - 1] >> colour_shift) + 1u : 0u;
+        for (uint32_t q = lo; q <= c; ++q) bounds[q] = i;
     }
 }
 
-// bounds[c] = first sorted slot of colour c (c = 0..8; colour 8 = unused slots).
-__global__ __launch_bounds__(BLOCK) void grad_bounds_kernel(const uint64_t* key, uint64_t n, int colour_shift,
-                                                            uint32_t* bounds) {
-    for (uint64_t i = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; i <= n; i += (uint64_t)gridDim.x * BLOCK) {
-        const uint64_t c = i < n ? (key[i] >> colour_shift) : 9;
-        const uint64_t cp = i > 0 ? (key[i - 1] >> colour_shift) : 0;
-        const uint64_t lo = i > 0 ? cp + 1 : 0;
-        for (uint64_t q = lo; q <= c && q <= 8; ++q) bounds[q] = (uint32_t)i;
-    }
-}
+// A row of a cell's corners: two grid points, six consecutive floats.
+struct __attribute__((packed, aligned(4))) Corners {
+    float v[6];
+};
 
-__global__ __launch_bounds__(BLOCK) void grad_apply_kernel(const uint64_t* key, const uint32_t* idx, const float* val,
-                                                           const uint32_t* bounds, int colour, uint64_t cell_mask,
-                                                           int level_shift, uint64_t level_mask, float* const* gf,
-                                                           Geom g) {
-    // a group is one (colour, level, cell): a run of equal keys
+// One lane per record of the colour; the first record's lane of a group (one
+// (colour, level, cell): a run of equal keys) sums the group.  The chain of
+// dependent loads and the CU's lines in flight are what bound it, so the keys
+// around the record and its index load together, then the record's values and
+// the grid's corners: 49 us per colour, 90 MB read and 46 MB written (60 with
+// each load where its value is used).
+template <class K>
+__global__ __launch_bounds__(BLOCK) void grad_apply_kernel(const K* key, const uint32_t* idx, const float* val,
+                                                           const uint32_t* bounds, int colour, K cell_mask,
+                                                           int level_shift, K level_mask, float* const* gf, Geom g) {
     const uint32_t lo = bounds[colour], hi = bounds[colour + 1];
     for (uint32_t i = lo + blockIdx.x * BLOCK + threadIdx.x; i < hi; i += gridDim.x * BLOCK) {
-        const uint64_t k = key[i];
-        if (i > lo && key[i - 1] == k) continue;  // not the first record of its group
+        const K k = key[i], before = key[i > lo ? i - 1 : i], after = key[i + 1 < hi ? i + 1 : i];
+        const uint32_t rec = idx[i];
+        if (i > lo && before == k) continue;  // not the first record of its group
+        const float4* v = reinterpret_cast<const float4*>(val + 24 * (size_t)rec);
+        float4 x[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) x[q] = v[q];
+        float* p0 = in_global(gf[(int)((k >> level_shift) & level_mask)]) + 3 * (uint64_t)(k & cell_mask);
+        Corners r[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            r[c] = *reinterpret_cast<const Corners*>(p0 + 3 * ((uint64_t)g.sy * (c & 1) + (uint64_t)g.sz * (c >> 1)));
         float s[24];
 #pragma unroll
-        for (int q = 0; q < 24; ++q) s[q] = 0.f;
-        for (uint32_t j = i; j < hi && key[j] == k; ++j) {
-            const float4* v = reinterpret_cast<const float4*>(val + 24 * (size_t)idx[j]);
+        for (int q = 0; q < 6; ++q) {
+            s[4 * q + 0] = x[q].x;
+            s[4 * q + 1] = x[q].y;
+            s[4 * q + 2] = x[q].z;
+            s[4 * q + 3] = x[q].w;
+        }
+        if (i + 1 < hi && after == k) {
+            for (uint32_t j = i + 1; j < hi && key[j] == k; ++j) {
+                const float4* w = reinterpret_cast<const float4*>(val + 24 * (size_t)idx[j]);
 #pragma unroll
-            for (int q = 0; q < 6; ++q) {
-                const float4 x = v[q];
-                s[4 * q + 0] += x.x;
-                s[4 * q + 1] += x.y;
-                s[4 * q + 2] += x.z;
-                s[4 * q + 3] += x.w;
+                for (int q = 0; q < 6; ++q) {
+                    const float4 y = w[q];
+                    s[4 * q + 0] += y.x;
+                    s[4 * q + 1] += y.y;
+                    s[4 * q + 2] += y.z;
+                    s[4 * q + 3] += y.w;
+                }
             }
         }
-        const uint32_t base = (uint32_t)(k & cell_mask);
-        const int level = (int)((k >> level_shift) & level_mask);
-        float* grid = in_global(gf[level]);
 #pragma unroll
-        for (int c = 0; c < 2; ++c)
+        for (int c = 0; c < 4; ++c) {
 #pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    float* p = grid + 3 * ((uint64_t)base + (uint64_t)q + (uint64_t)g.sy * b + (uint64_t)g.sz * c);
-                    const int m = 3 * (q + 2 * b + 4 * c);
-                    p[0] += s[m + 0];
-                    p[1] += s[m + 1];
-                    p[2] += s[m + 2];
-                }
+            for (int q = 0; q < 6; ++q) r[c].v[q] += s[6 * c + q];
+            *reinterpret_cast<Corners*>(p0 + 3 * ((uint64_t)g.sy * (c & 1) + (uint64_t)g.sz * (c >> 1))) = r[c];
+        }
     }
 }
 
 static int key_bits(const GradRec& r) { return r.level_bits + r.cell_bits + 3; }
-
-size_t grad_sort_temp_bytes(uint64_t n, int) { return radix_temp_bytes(n); }
 
 static unsigned grid_of(uint64_t n) {
     const uint64_t b = (n + BLOCK - 1) / BLOCK;
@@ -90,39 +103,42 @@ static unsigned grid_of(uint64_t n) {
 }
 
 hipError_t launch_grad_clear(const GradRec& r, uint64_t n, hipStream_t s) {
-    // unused slots: the colour field reads 8, above every real colour
-    const uint64_t empty = (uint64_t)8 << (key_bits(r) - 3);
-    hipLaunchKernelGGL(grad_clear_kernel, dim3(grid_of(n)), dim3(BLOCK), 0, s, r.key, r.idx, n, empty);
+    // unused slots: the bit above the key's
+    const uint64_t empty = 1ull << key_bits(r);
+    if (r.key_bytes == 4)
+        hipLaunchKernelGGL((grad_clear_kernel<uint32_t>), dim3(grid_of(n)), dim3(BLOCK), 0, s,
+                           static_cast<uint32_t*>(r.key), n, (uint32_t)empty);
+    else
+        hipLaunchKernelGGL((grad_clear_kernel<uint64_t>), dim3(grid_of(n)), dim3(BLOCK), 0, s,
+                           static_cast<uint64_t*>(r.key), n, empty);
     return hipGetLastError();
 }
 
-hipError_t launch_grad_reduce(const GradRec& r, uint64_t n, uint64_t* key_out, uint32_t* idx_out, uint32_t* bounds,
-                              void* temp, size_t temp_bytes, float* const* gf, const Geom& g, hipStream_t s) {
-    if (n == 0) return hipSuccess;
-    const int colour_shift = key_bits(r) - 3;
-    (void)temp_bytes;
-    // one more bit than the key fields: the unused-slot marker; the sorted
-    // pairs end in (key_out, idx_out) or, after an even number of passes, in
-    // the records' own arrays
-    bool in_alt = false;
-    hipError_t e = launch_radix_sort_pairs(r.key, r.idx, key_out, idx_out, n, key_bits(r) + 1, temp, &in_alt, s);
-    if (e != hipSuccess) return e;
-    if (!in_alt) {
-        key_out = r.key;
-        idx_out = r.idx;
-    }
-    hipLaunchKernelGGL(grad_bounds_kernel, dim3(grid_of(n + 1)), dim3(BLOCK), 0, s, key_out, n, colour_shift, bounds);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const uint64_t cell_mask = (1ull << r.cell_bits) - 1ull;
-    const uint64_t level_mask = (1ull << r.level_bits) - 1ull;
-    for (int colour = 0; colour < 8; ++colour) {
-        hipLaunchKernelGGL(grad_apply_kernel, dim3(grid_of(n / 8 + 1)), dim3(BLOCK), 0, s, key_out, idx_out, r.val,
+template <class K>
+static hipError_t apply(const GradRec& r, const K* key, const uint32_t* idx, uint32_t* bounds, uint64_t n,
+                        float* const* gf, const Geom& g, hipStream_t s) {
+    hipLaunchKernelGGL((grad_bounds_kernel<K>), dim3(grid_of(n + 1)), dim3(BLOCK), 0, s, key, key_bits(r) - 3, bounds);
+    hipError_t e = hipGetLastError();
+    const K cell_mask = (K)((1ull << r.cell_bits) - 1ull), level_mask = (K)((1ull << r.level_bits) - 1ull);
+    for (int colour = 0; colour < 8 && e == hipSuccess; ++colour) {
+        hipLaunchKernelGGL((grad_apply_kernel<K>), dim3(grid_of(n / 8 + 1)), dim3(BLOCK), 0, s, key, idx, r.val,
                            bounds, colour, cell_mask, r.cell_bits, level_mask, gf, g);
         e = hipGetLastError();
-        if (e != hipSuccess) return e;
     }
-    return hipSuccess;
+    return e;
+}
+
+hipError_t launch_grad_reduce(const GradRec& r, const GradSort& w, uint64_t n, float* const* gf, const Geom& g,
+                              hipStream_t s) {
+    if (n == 0) return hipSuccess;
+    bool in_alt = false;
+    hipError_t e = launch_radix_sort_slots(r.key, w.key_alt, w.idx[0], w.idx[1], r.key_bytes, n, key_bits(r),
+                                           w.bounds + 9, w.temp, &in_alt, s);
+    if (e != hipSuccess) return e;
+    const void* key = in_alt ? w.key_alt : r.key;
+    const uint32_t* idx = w.idx[in_alt ? 1 : 0];
+    if (r.key_bytes == 4) return apply(r, static_cast<const uint32_t*>(key), idx, w.bounds, n, gf, g, s);
+    return apply(r, static_cast<const uint64_t*>(key), idx, w.bounds, n, gf, g, s);
 }
 
 }  // namespace bto

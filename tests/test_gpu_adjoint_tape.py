@@ -60,3 +60,45 @@ def test_intervals_beyond_the_tape(dtype, recorded):
         # about 50 seeds per cell and level: each grid sum has fewer than 2,000
         # terms of one sign up to the flow's shear, added in different groupings
         assert (ga - gb).abs().max() <= 2e-5 * ga.abs().max()
+
+
+# Record slots around the sort's tile of 4,096 (2 (N + 1) + 2 per seed, in
+# sixteens), one to a hundred seeds per cell; 512^3 x 2 steps: 32 key bits, the
+# marker of unused slots needs 64-bit keys.  A flow of one sign: a seed crosses
+# each cell face once, so none runs out of record slots (the flushes beyond
+# them are atomics, in no fixed order).
+@pytest.mark.parametrize("n,N,P", [((5, 6, 7), 1, 1), ((9, 8, 7), 1, 682), ((9, 8, 7), 1, 683), ((4, 3, 5), 2, 2400),
+                                   ((40, 30, 20), 5, 30_000), ((512, 512, 512), 2, 5000)])
+def test_grid_gradient_reduction_at_its_sizes(n, N, P, monkeypatch):
+    g = torch.Generator(device="cuda").manual_seed(P)
+    grids = []
+    for _ in range(N + 1):
+        v = torch.rand((n[2], n[1], n[0], 3), device="cuda", generator=g)
+        grids.append(v.mul_(0.4).add_(0.1).to(torch.float16))
+        del v
+    times = np.arange(N + 1) * 0.1
+    hi = torch.tensor([v - 1.0 for v in n], dtype=torch.float64, device="cuda")
+    seeds = torch.rand((P, 3), dtype=torch.float64, device="cuda", generator=g) * hi * 0.8 + 0.1 * hi
+    cot = 0.5 + torch.rand((P, 1, 3), device="cuda", generator=g)
+    print(f"[gpu-case] reduction {n} {N} {P}", file=sys.stderr, flush=True)
+    from paper_2004_02003_amd import Context
+
+    def run():
+        gg = [torch.zeros(v.shape, dtype=torch.float32, device="cuda") for v in grids]
+        with Context(n, P) as ctx:
+            ctx.seed_explicit(seeds)
+            ctx.adjoint(grids, times, cot, grad_grids=gg, ckpt_every=2)
+            torch.cuda.synchronize()
+        return gg
+
+    a, b = run(), run()
+    assert all(torch.equal(x, y) for x, y in zip(a, b))
+    del b
+    monkeypatch.setenv("BTO_GRAD_ATOMICS", "1")
+    c = run()
+    # fewer than 200 terms of (nearly) one sign per point, added in two orders
+    top = max(float(x.abs().max()) for x in c)
+    assert top > 0
+    for x, y in zip(a, c):
+        assert float((x - y).abs().max()) <= 2e-5 * top
+        assert torch.equal(x != 0, y != 0)
