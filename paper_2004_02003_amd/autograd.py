@@ -48,7 +48,10 @@ class BTOAdvectFn(torch.autograd.Function):
         if not recorded:
             bctx.seed_explicit(s)
         want_grids = any(fctx.needs_input_grad[5:])
-        gg = [torch.zeros(g.shape, dtype=torch.float32, device=g.device) for g in grids] if want_grids else None
+        gg = None
+        if want_grids:
+            gg = [torch.empty(g.shape, dtype=torch.float32, device=g.device) for g in grids]
+            torch._foreach_zero_(gg)  # a few launches for all grids
         cot = g_end.to(torch.float32).contiguous()
         gs = bctx.adjoint(grids, fctx.times, cot, grad_grids=gg, ckpt_every=fctx.ckpt_every, mode=fctx.mode,
                           recorded=recorded)
