@@ -896,11 +896,9 @@ int bto_reconstruct_lattice(const int32_t m[3], double* d_end_xyz, const uint8_t
 int bto_flowmap_error(int64_t n, const double* d_b_xyz, const uint8_t* d_b_state, const double* d_m_xyz,
                       const uint8_t* d_m_flag, double cell, double* out5, void* stream) {
     if (n < 1 || !d_b_xyz || !d_b_state || !d_m_xyz || !d_m_flag || !out5 || !(cell > 0.0)) return BTO_EINVAL;
-    void* scratch = nullptr;
-    if (hipMalloc(&scratch, err_scratch_bytes(n)) != hipSuccess) return BTO_ENOMEM;
     double r[4];
-    const hipError_t e = launch_flowmap_error(n, d_b_xyz, d_b_state, d_m_xyz, d_m_flag, scratch, r, (hipStream_t)stream);
-    (void)hipFree(scratch);
+    const hipError_t e = flowmap_error(n, d_b_xyz, d_b_state, d_m_xyz, d_m_flag, r, (hipStream_t)stream);
+    if (e == hipErrorOutOfMemory) return BTO_ENOMEM;
     if (e != hipSuccess) return BTO_EHIP;
     const double mean = r[2] > 0 ? r[0] / r[2] : 0.0;
     out5[0] = mean;

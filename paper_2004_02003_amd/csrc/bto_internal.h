@@ -348,6 +348,10 @@ hipError_t launch_advect(const AdvectArgs& a, int dtype, int mode, int lanes_per
 hipError_t launch_exit_points(const FlowmapArgs& a, hipStream_t s);
 hipError_t launch_reconstruct(const int32_t m[3], double* end, const uint8_t* flag, uint8_t* state, hipStream_t s);
 size_t err_scratch_bytes(int64_t P);
+// The accuracy metric with scratch of its own kept between calls (see there);
+// launch_flowmap_error: with the caller's.  Both wait for the stream.
+hipError_t flowmap_error(int64_t P, const double* b, const uint8_t* bstate, const double* m, const uint8_t* mflag,
+                         double out4[4], hipStream_t s);
 hipError_t launch_flowmap_error(int64_t P, const double* b, const uint8_t* bstate, const double* m, const uint8_t* mflag,
                                 void* scratch, double out4[4], hipStream_t s);
 // This GPU's copy of the fixed scratch of the allocation-free metric (looked
