@@ -25,10 +25,26 @@ def _flags(mode: str, record_exit: bool = False, record_ckpt: bool = False, fp64
             | (_lib.BTO_RECORD_CKPT if record_ckpt else 0) | (_lib.BTO_SAMPLE_FP64 if fp64 else 0))
 
 
+# The current stream's handle without a Stream object around it (2.9 us a call).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
+        if _raw_stream is not None:
+            return _raw_stream(torch.cuda.current_device())
         stream = torch.cuda.current_stream()
     return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
+
+
+def _doubles(times):
+    """Host doubles to pass to the library (a short tuple without numpy: 1.3 us less)."""
+    if type(times) is tuple:
+        try:
+            return (ctypes.c_double * len(times))(*times)
+        except TypeError:
+            pass
+    return np.ascontiguousarray(np.asarray(times, dtype=np.float64)).ctypes.data_as(ctypes.c_void_p)
 
 
 def grid_to_device(grid: np.ndarray, dtype: str, device="cuda") -> torch.Tensor:
@@ -163,8 +179,8 @@ class Context:
                     record_ckpt: bool = False, fp64: bool = False):
         """Same as ``advect`` with raw device pointers (no per-call tensor checks)."""
         arr = (ctypes.c_void_p * len(ptrs))(*ptrs)
-        t = np.ascontiguousarray(np.asarray(times, dtype=np.float64))
-        self._check(self.L.bto_advect_interval(self._h, arr, t.ctypes.data, len(ptrs) - 1, int(dtype),
+        t = _doubles(times)
+        self._check(self.L.bto_advect_interval(self._h, arr, t, len(ptrs) - 1, int(dtype),
                                                _flags(mode, record_exit, record_ckpt, fp64), _stream_ptr(stream)))
         self.steps_advected = getattr(self, "steps_advected", 0) + len(ptrs) - 1
 

@@ -27,17 +27,21 @@ import numpy as np
 import torch
 
 from . import _lib
-from .context import BTOError, Context
+from .context import BTOError, Context, _stream_ptr
 
 MISSING, KNOWN, REBUILT = 0, 1, 2
 
 
+_I3 = ctypes.c_int32 * 3
+_D3 = ctypes.c_double * 3
+
+
 def _i3(v) -> ctypes.Array:
-    return (ctypes.c_int32 * 3)(*[int(x) for x in v])
+    return _I3(*[int(x) for x in v])
 
 
 def _stream(stream) -> int:
-    return (stream or torch.cuda.current_stream()).cuda_stream
+    return stream.cuda_stream if stream else _stream_ptr(None)
 
 
 def _check(rc: int, what: str):
@@ -50,7 +54,7 @@ def place_block(src_end: torch.Tensor, src_flag: torch.Tensor, mb, dst_end: torc
     """Copy a block's seed-ordered flow map (lattice mb) into the lattice M at
     offset off, adding ``shift`` to the positions."""
     L = _lib.load()
-    sh = (ctypes.c_double * 3)(*[float(v) for v in shift])
+    sh = _D3(*[float(v) for v in shift])
     _check(L.bto_place_block(_i3(mb), _i3(M), _i3(off), sh, src_end.data_ptr(), src_flag.data_ptr(),
                              dst_end.data_ptr(), dst_flag.data_ptr(), _stream(stream)), "bto_place_block")
 
