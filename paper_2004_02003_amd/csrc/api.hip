@@ -592,6 +592,7 @@ static int rebin(bto_ctx* c, hipStream_t s) {
     a.hist = c->rebin_buf + 2 * (size_t)c->cap;
     a.offs = a.hist + (size_t)NSEG * nbins;
     a.nbins = nbins;
+    while (((uint64_t)NSEG * nbins - 1) >> a.bin_bits) ++a.bin_bits;
     a.nbx = nb[0];
     a.nby = nb[1];
     a.temp = c->rebin_temp;

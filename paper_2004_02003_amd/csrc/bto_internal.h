@@ -220,6 +220,7 @@ struct RebinArgs {
     uint32_t* hist;            // NSEG * nbins counts (all zero between rebins)
     uint32_t* offs;            // NSEG * nbins exclusive prefix sums
     uint32_t nbins;            // bins per segment
+    int32_t bin_bits;          // bits of a bin's number (segment and bin)
     uint32_t nbx, nby;         // bins along x and y
     void* temp;
     size_t temp_bytes;

@@ -8,8 +8,9 @@
 // along a few grid rows, so each of a cell's row loads covers long runs of
 // contiguous memory -- the same reason the lattice is seeded x-fastest), with
 // a counting sort:
-//   count   - per particle, atomically increment its (segment, bin) counter;
-//             the old value is the particle's rank inside the bin;
+//   count   - atomically add to each (segment, bin) counter, once for a
+//             wavefront's particles of the bin; the old value and the place
+//             among them are a particle's rank inside the bin;
 //   scan    - exclusive prefix sum over all bins (segment-major; radix.hip);
 //   scatter - move each particle to its segment base + bin offset + rank, and
 //             zero its bin for the next rebin.
@@ -26,16 +27,36 @@ __device__ __forceinline__ int segment_of(const Segs& sg, int64_t i) {
     return seg;
 }
 
+// The counters are memory atomics whose old value is needed, and those bound
+// the kernel (2 million particles of a 256^3 turbulence block, re-sorted every
+// 5 steps: 98 us with one atomic each, 40 now).  Most of a wavefront's particles
+// still share their bins, so the lanes of one bin, found with a ballot per bit
+// of the bin number, send one atomic together.
 __global__ __launch_bounds__(BLOCK) void rebin_count_kernel(const RebinArgs a) {
-    for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < a.P; i += (int64_t)gridDim.x * BLOCK) {
+    const unsigned long long lt = (1ull << (threadIdx.x % WAVE)) - 1ull;
+    const int64_t n = (a.P + WAVE - 1) / WAVE * WAVE;  // whole wavefronts stay together
+    for (int64_t i = (int64_t)blockIdx.x * BLOCK + threadIdx.x; i < n; i += (int64_t)gridDim.x * BLOCK) {
         const int seg = segment_of(a.segs, i);
-        if (i - a.segs.base[seg] >= (int64_t)a.count[seg * CSTRIDE]) continue;  // slot beyond the segment's live count
-        const uint32_t c = a.pos[i].cell;
+        // (slots beyond the segment's live count hold none)
+        const bool live = i < a.P && i - a.segs.base[seg] < (int64_t)a.count[seg * CSTRIDE];
+        const uint32_t c = live ? a.pos[i].cell : 0u;
         const uint32_t key = (c & 1023u) / REBIN_BIN[0] +
                              a.nbx * (((c >> 10) & 1023u) / REBIN_BIN[1] + a.nby * (((c >> 20) & 1023u) / REBIN_BIN[2]));
         const uint32_t bin = (uint32_t)seg * a.nbins + key;
-        a.bin[i] = bin;
-        a.rank[i] = atomicAdd(&a.hist[bin], 1u);
+        unsigned long long peers = __ballot(live);
+        if (!peers) continue;
+        for (int b = 0; b < a.bin_bits; ++b) {
+            const unsigned long long m = __ballot((bin >> b) & 1u);
+            peers &= (bin >> b) & 1u ? m : ~m;
+        }
+        const int first = live ? __ffsll((long long)peers) - 1 : 0;
+        uint32_t old = 0u;
+        if (live && !(peers & lt)) old = atomicAdd(&a.hist[bin], (uint32_t)__popcll(peers));
+        const uint32_t base = __shfl(old, first);
+        if (live) {
+            a.bin[i] = bin;
+            a.rank[i] = base + (uint32_t)__popcll(peers & lt);
+        }
     }
 }
 
