@@ -444,8 +444,7 @@ static int tile_enter(bto_ctx* c, int dtype, int max_seg_blocks, hipStream_t s) 
 
 // Live particles of the tile layout, by seed id: flow-map entries (out_end
 // non-null) or FP64 positions into a checkpoint slot (ckpt non-null).
-static int tile_live(bto_ctx* c, double* out_end, uint8_t* out_flag, int32_t* out_exit, double* ckpt,
-                     hipStream_t s) {
+static int tile_live(bto_ctx* c, double* out_end, double* ckpt, hipStream_t s) {
     TileLiveArgs a{};
     a.ntiles = (uint32_t)c->tile_grid;
     a.cap = c->tcap;
@@ -455,15 +454,13 @@ static int tile_live(bto_ctx* c, double* out_end, uint8_t* out_flag, int32_t* ou
     a.list_pos = c->pos[c->cur];
     a.list_id = c->id[c->cur];
     a.list_count = c->lcount + c->slot;
-    a.list_n_max = (uint64_t)c->n_seeds;
-    a.steps_done = c->steps_done;
+    const int64_t lb = (c->n_seeds + BLOCK - 1) / BLOCK;
+    a.list_blocks = (uint32_t)(lb < 1024 ? lb : 1024);
     for (int d = 0; d < 3; ++d) {
         a.origin[d] = c->blk.origin[d];
         a.spacing[d] = c->blk.spacing[d];
     }
     a.out_end = out_end;
-    a.out_flag = out_flag;
-    a.out_exit = out_exit;
     a.ckpt = ckpt;
     hipError_t e = launch_tile_live(a, s);
     return e == hipSuccess ? BTO_OK : hip_fail(c, e, "tile live launch");
@@ -745,8 +742,7 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
         }
         for (int32_t q = 0; q < n_steps; ++q) {
             if (store_ck && c->steps_done % c->ck_k == 0) {
-                rc = tile_live(c, nullptr, nullptr, nullptr,
-                               c->ck_rec + (size_t)(c->steps_done / c->ck_k) * (size_t)c->cap * 3, s);
+                rc = tile_live(c, nullptr, c->ck_rec + (size_t)(c->steps_done / c->ck_k) * (size_t)c->cap * 3, s);
                 if (rc) return rc;
             }
             rc = tile_step(c, d_fields[q], d_fields[q + 1], times[q + 1] - times[q], dtype, mode, rec, s);
@@ -847,7 +843,7 @@ int bto_flowmap_out(bto_ctx* c, double* d_seed_xyz, double* d_end_xyz, uint8_t* 
         hipError_t e = launch_flowmap(a, c->tile_layout ? 0 : blocks_per_seg(c, max_seg, 4), s);
         if (e != hipSuccess) return hip_fail(c, e, "flowmap launch");
         if (c->tile_layout) {
-            rc = tile_live(c, d_end_xyz, d_flag, d_exit_step, nullptr, s);
+            rc = tile_live(c, d_end_xyz, nullptr, s);
             if (rc) return rc;
         }
     }

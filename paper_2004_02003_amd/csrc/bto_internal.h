@@ -321,12 +321,9 @@ struct TileLiveArgs {
     const PState* list_pos;
     const uint32_t* list_id;
     const uint32_t* list_count;
-    uint64_t list_n_max;
-    int32_t steps_done;
+    uint32_t list_blocks;     // workgroups for the list
     double origin[3], spacing[3];
     double* out_end;          // flow map (ckpt == null)
-    uint8_t* out_flag;
-    int32_t* out_exit;
     double* ckpt;             // checkpoint slot base: [seed id][xyz] (cell units)
 };
 
