@@ -36,62 +36,45 @@ __global__ __launch_bounds__(BLOCK) void grad_bounds_kernel(const K* key, int co
     }
 }
 
-// A row of a cell's corners: two grid points, six consecutive floats.
-struct __attribute__((packed, aligned(4))) Corners {
-    float v[6];
+// A corner's gradient.
+struct __attribute__((packed, aligned(4))) Corner {
+    float v[3];
 };
 
-// One lane per record of the colour; the first record's lane of a group (one
-// (colour, level, cell): a run of equal keys) sums the group.  The chain of
-// dependent loads and the CU's lines in flight are what bound it, so the keys
-// around the record and its index load together, then the record's values and
-// the grid's corners: 49 us per colour, 90 MB read and 46 MB written (60 with
-// each load where its value is used).
+// Eight lanes per record of the colour, one per corner; those of the first
+// record of a group (one (colour, level, cell): a run of equal keys) sum the
+// group.  The grids' lines bound it, 90 MB read and 46 MB written per colour: 46
+// us.  With a lane per record (six 16-byte loads 96 bytes apart from lane to
+// lane, eight 12-byte corners) 49 us, and 60 with each load where its value is
+// used; so the keys around the record and its index load together, then the
+// corner's gradient and the grid's.
 template <class K>
 __global__ __launch_bounds__(BLOCK) void grad_apply_kernel(const K* key, const uint32_t* idx, const float* val,
                                                            const uint32_t* bounds, int colour, K cell_mask,
                                                            int level_shift, K level_mask, float* const* gf, Geom g) {
     const uint32_t lo = bounds[colour], hi = bounds[colour + 1];
-    for (uint32_t i = lo + blockIdx.x * BLOCK + threadIdx.x; i < hi; i += gridDim.x * BLOCK) {
+    const uint32_t corner = threadIdx.x % 8;
+    const uint64_t step = 3 * ((uint64_t)(corner & 1) + (uint64_t)g.sy * (corner >> 1 & 1) +
+                               (uint64_t)g.sz * (corner >> 2));
+    const float* v0 = val + 3 * corner;
+    for (uint32_t i = lo + (blockIdx.x * BLOCK + threadIdx.x) / 8; i < hi; i += gridDim.x * (BLOCK / 8)) {
         const K k = key[i], before = key[i > lo ? i - 1 : i], after = key[i + 1 < hi ? i + 1 : i];
         const uint32_t rec = idx[i];
         if (i > lo && before == k) continue;  // not the first record of its group
-        const float4* v = reinterpret_cast<const float4*>(val + 24 * (size_t)rec);
-        float4 x[6];
-#pragma unroll
-        for (int q = 0; q < 6; ++q) x[q] = v[q];
-        float* p0 = in_global(gf[(int)((k >> level_shift) & level_mask)]) + 3 * (uint64_t)(k & cell_mask);
-        Corners r[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-            r[c] = *reinterpret_cast<const Corners*>(p0 + 3 * ((uint64_t)g.sy * (c & 1) + (uint64_t)g.sz * (c >> 1)));
-        float s[24];
-#pragma unroll
-        for (int q = 0; q < 6; ++q) {
-            s[4 * q + 0] = x[q].x;
-            s[4 * q + 1] = x[q].y;
-            s[4 * q + 2] = x[q].z;
-            s[4 * q + 3] = x[q].w;
-        }
+        Corner s = *reinterpret_cast<const Corner*>(v0 + 24 * (size_t)rec);
+        Corner* p = reinterpret_cast<Corner*>(in_global(gf[(int)((k >> level_shift) & level_mask)]) +
+                                              3 * (uint64_t)(k & cell_mask) + step);
+        const Corner old = *p;
         if (i + 1 < hi && after == k) {
             for (uint32_t j = i + 1; j < hi && key[j] == k; ++j) {
-                const float4* w = reinterpret_cast<const float4*>(val + 24 * (size_t)idx[j]);
+                const Corner y = *reinterpret_cast<const Corner*>(v0 + 24 * (size_t)idx[j]);
 #pragma unroll
-                for (int q = 0; q < 6; ++q) {
-                    const float4 y = w[q];
-                    s[4 * q + 0] += y.x;
-                    s[4 * q + 1] += y.y;
-                    s[4 * q + 2] += y.z;
-                    s[4 * q + 3] += y.w;
-                }
+                for (int d = 0; d < 3; ++d) s.v[d] += y.v[d];
             }
         }
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-#pragma unroll
-            for (int q = 0; q < 6; ++q) r[c].v[q] += s[6 * c + q];
-            *reinterpret_cast<Corners*>(p0 + 3 * ((uint64_t)g.sy * (c & 1) + (uint64_t)g.sz * (c >> 1))) = r[c];
-        }
+        for (int d = 0; d < 3; ++d) s.v[d] = old.v[d] + s.v[d];
+        *p = s;
     }
 }
 
@@ -121,7 +104,7 @@ static hipError_t apply(const GradRec& r, const K* key, const uint32_t* idx, uin
     hipError_t e = hipGetLastError();
     const K cell_mask = (K)((1ull << r.cell_bits) - 1ull), level_mask = (K)((1ull << r.level_bits) - 1ull);
     for (int colour = 0; colour < 8 && e == hipSuccess; ++colour) {
-        hipLaunchKernelGGL((grad_apply_kernel<K>), dim3(grid_of(n / 8 + 1)), dim3(BLOCK), 0, s, key, idx, r.val,
+        hipLaunchKernelGGL((grad_apply_kernel<K>), dim3(grid_of(n)), dim3(BLOCK), 0, s, key, idx, r.val,
                            bounds, colour, cell_mask, r.cell_bits, level_mask, gf, g);
         e = hipGetLastError();
     }
