@@ -251,7 +251,9 @@ int bto_get_tuning(const bto_ctx *ctx, bto_tuning *t);
  * of RK4 with the trilinear sampler's gradient on the cell chosen by the
  * floor/clamp rule.  An interval whose stages pass 1 GiB (64 bytes per step
  * and seed) is swept in groups of segments of ckpt_every steps, each
- * recomputed from the positions at its first step.
+ * recomputed from the positions at its first step.  With n_cot = 3, no grid
+ * gradients and no recorded checkpoints the same derivatives are carried along
+ * the forward steps instead (one sweep, nothing kept).
  *   d_cot_end  (n_seeds x n_cot x 3 floats, world units): cotangents of the
  *              end positions; n_cot = 1 (a scalar loss L = sum c . x_end) or
  *              3 (one per axis: d_grad_seed then holds the 3x3 flow-map

@@ -29,12 +29,15 @@
 // wavefronts ask for.  So the reverse sweep asks for each line once: a lane
 // loads a stage's cell only where it differs from the neighbouring stage's, and
 // level n + 1 is kept from the step before; loading all six cells of a step
-// took 330 us instead of 223 (Jacobian of 48,960 seeds over 49 steps, 160 x 144
-// x 136 f16 turbulence) and 316 instead of 231 (gradient of 32,768 seeds over
-// 50 steps, 128^3 ABC, f32; 372 without the loads a step ahead).  The forward
-// takes 266 us there, the recompute of five segments 174.  One sweep that
-// recomputed and reversed one segment after the other, each step in dependent
-// loads, took 935 and 541 us in all.
+// took 316 us instead of 231 (gradient of 32,768 seeds over 50 steps, 128^3 ABC,
+// f32; 372 without the loads a step ahead) and 330 instead of 220 (three
+// cotangents of 48,960 seeds over 49 steps, 160 x 144 x 136 f16 turbulence).
+// The recompute of five segments takes 174 us in the first, the forward 264 in
+// the second.  One sweep that recomputed and reversed one segment after the
+// other, each step in dependent loads, took 541 and 935 us in all.
+//
+// The Jacobian of a recomputed interval needs no reverse sweep at all: see
+// adj_tangent_kernel.
 #include "bto_internal.h"
 
 namespace bto {
@@ -135,37 +138,33 @@ __device__ __forceinline__ void acc_add(const Geom& g, float* const* gf, const G
 // packing four of them onto each of the first P/256 CUs.
 constexpr int ADJ_BLOCK = WAVE;
 
-// Steps n0 .. n1 - 1 from st.x, the advection's own step; tape entries of step
-// n at t + 4 * np * (n - n0) (t null: none).  Returns the status of the step
-// that ended it, or S_VALID.
-template <int DT, int MODE>
-__device__ __forceinline__ int adj_steps(const AdjointArgs& a, double* x, int n0, int n1, TapeEntry* t, bool ck) {
+// Steps n0 .. n1 - 1 from x, the advection's own step.  hook.begin(n, h, x)
+// before step n; hook.stage(n, s, c) with the cell and the offsets stage s
+// samples; hook.sample(s, c, A, B) with its corner values; hook.end() after a
+// step that stayed inside.  Returns the status of the step that ended it, or
+// S_VALID.
+template <int DT, int MODE, class Hook>
+__device__ __forceinline__ int adj_steps(const AdjointArgs& a, double* x, int n0, int n1, Hook& hook) {
     GatherCache<DT> A, B;
     forget(A);
     forget(B);
     int status = S_VALID;
     const auto step = [&](int n, GatherCache<DT>& LA, GatherCache<DT>& LB) {
-        if (ck && n % a.k == 0) {
-            double* c = a.ckpt + a.ck_stride * (int64_t)(n / a.k) + 3 * (a.p0 + (int64_t)blockIdx.x * ADJ_BLOCK + threadIdx.x);
-#pragma unroll
-            for (int d = 0; d < 3; ++d) c[d] = x[d];
-        }
-        StepSizes hs = step_sizes(a.g, scalar_load(a.h + (n - a.f_base)));
+        const double h = scalar_load(a.h + (n - a.f_base));
+        hook.begin(n, h, x);
+        StepSizes hs = step_sizes(a.g, h);
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             hs.full[d] = uniform(hs.full[d]);
             hs.half[d] = uniform(hs.half[d]);
             hs.sixth[d] = uniform(hs.sixth[d]);
         }
-        const auto on_stage = [&](int s, const GatherCell<float>& c) {
-            if (t) {
-                const U4 e = {c.val, __float_as_uint(c.f[0]), __float_as_uint(c.f[1]), __float_as_uint(c.f[2])};
-                *reinterpret_cast<U4*>(t + a.np * (int64_t)(4 * (n - n0) + s)) = e;
-            }
-        };
         status = rk4_step_gather<DT, MODE>(a.g, in_global(scalar_load(a.f + (n - a.f_base))),
                                            in_global(scalar_load(a.f + (n + 1 - a.f_base))), hs, x, LA, LB, false,
-                                           [](const double*) {}, on_stage);
+                                           [](const double*) {},
+                                           [&](int s, const GatherCell<float>& c) { hook.stage(n, s, c); },
+                                           [&](int s, const GatherCell<float>& c) { hook.sample(s, c, LA, LB); });
+        if (status == S_VALID) hook.end();
         forget(LA);  // receives level n + 2
         if (is_frozen<MODE>) forget(LB);
     };
@@ -178,6 +177,104 @@ __device__ __forceinline__ int adj_steps(const AdjointArgs& a, double* x, int n0
     return status;
 }
 
+// The tape of steps n0 on at t (null: none), checkpoints every a.k steps at ck
+// (null: none).
+struct TapeHook {
+    const AdjointArgs& a;
+    TapeEntry* t;
+    double* ck;
+    int n0;
+    __device__ __forceinline__ void begin(int n, double, const double* x) const {
+        if (!ck || n % a.k != 0) return;
+        double* c = ck + a.ck_stride * (int64_t)(n / a.k);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) c[d] = x[d];
+    }
+    __device__ __forceinline__ void stage(int n, int s, const GatherCell<float>& c) const {
+        if (!t) return;
+        const U4 e = {c.val, __float_as_uint(c.f[0]), __float_as_uint(c.f[1]), __float_as_uint(c.f[2])};
+        *reinterpret_cast<U4*>(t + a.np * (int64_t)(4 * (n - n0) + s)) = e;
+    }
+    template <class C>
+    __device__ __forceinline__ void sample(int, const GatherCell<float>&, const C&, const C&) const {}
+    __device__ __forceinline__ void end() const {}
+};
+
+// The tangent T = d x_n / d x_0 (cell units) carried along the steps: dk_s =
+// G_s dy_s with the stage points' derivatives dy_s, as the step combines the
+// stage velocities.
+template <int MODE>
+struct TangentHook {
+    const Geom& g;
+    float T[3][3], Y[3][3], S[3][3], h;
+    __device__ __forceinline__ void begin(int, double hd, const double*) {
+        h = (float)hd;
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) Y[r][c] = T[r][c];
+    }
+    __device__ __forceinline__ void stage(int, int, const GatherCell<float>&) const {}
+    template <class C>
+    __device__ __forceinline__ void sample(int s, const GatherCell<float>& c, const C& A, const C& B) {
+        constexpr bool lin = !is_frozen<MODE>;
+        float unused[3], D[3][3];
+        if (lin && (s == 1 || s == 2)) trilerp_grad<lin>(A.rows(g), B.rows(g), c.f, unused, D);
+        else if (lin && s == 3) trilerp_grad<false>(B.rows(g), B.rows(g), c.f, unused, D);
+        else trilerp_grad<false>(A.rows(g), A.rows(g), c.f, unused, D);
+        const float w = s == 0 || s == 3 ? 1.f : 2.f, next = s < 2 ? 0.5f * h : h;
+        float K[3][3];
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int k = 0; k < 3; ++k)
+                K[r][k] = (float)g.inv_sp[r] * (D[r][0] * Y[0][k] + D[r][1] * Y[1][k] + D[r][2] * Y[2][k]);
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int k = 0; k < 3; ++k) {
+                S[r][k] = s == 0 ? K[r][k] : S[r][k] + w * K[r][k];
+                Y[r][k] = T[r][k] + next * K[r][k];
+            }
+    }
+    __device__ __forceinline__ void end() {
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) T[r][c] = T[r][c] + (h / 6.f) * S[r][c];
+    }
+};
+
+// Three cotangents of the adjoint's own forward, without grid gradients (the
+// flow-map Jacobian): the tangent along the forward sweep instead of a tape and
+// a reverse sweep, whose loads it does without: 300 us where the two sweeps take
+// 264 and 220 (48,960 seeds, 49 steps, 160 x 144 x 136 f16 turbulence); the
+// derivatives alone cost the forward sweep 36.  With grid gradients, or from
+// checkpoints whose segments recompute in parallel, the reverse sweep stays.
+template <int DT, int MODE>
+__global__ __launch_bounds__(ADJ_BLOCK) void adj_tangent_kernel(const AdjointArgs a) {
+    const int64_t p = (int64_t)blockIdx.x * ADJ_BLOCK + threadIdx.x;
+    if (p >= a.P) return;
+    double x[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) x[d] = (a.seed_xyz[3 * p + d] - a.origin[d]) * a.g.inv_sp[d];
+    TangentHook<MODE> hook{a.g, {{1.f, 0.f, 0.f}, {0.f, 1.f, 0.f}, {0.f, 0.f, 1.f}}, {}, {}, 0.f};
+    int status = S_TERMINATED;
+    if (inside(a.g, x)) status = adj_steps<DT, MODE>(a, x, 0, a.N, hook);
+    if (a.status_out) a.status_out[p] = (uint8_t)status;
+#pragma unroll
+    for (int m = 0; m < 3; ++m) {
+        float l[3];
+#pragma unroll
+        for (int r = 0; r < 3; ++r) l[r] = status == S_VALID ? a.cot[9 * p + 3 * m + r] * (float)a.sp[r] : 0.f;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const float v = hook.T[0][d] * l[0] + hook.T[1][d] * l[1] + hook.T[2][d] * l[2];
+            a.grad_seed[9 * p + 3 * m + d] = status == S_VALID ? v * (float)a.g.inv_sp[d] : 0.f;
+        }
+    }
+}
+
 template <int DT, int MODE>
 __global__ __launch_bounds__(ADJ_BLOCK) void adj_forward_kernel(const AdjointArgs a) {
     const int64_t q = (int64_t)blockIdx.x * ADJ_BLOCK + threadIdx.x, p = a.p0 + q;
@@ -186,7 +283,8 @@ __global__ __launch_bounds__(ADJ_BLOCK) void adj_forward_kernel(const AdjointArg
 #pragma unroll
     for (int d = 0; d < 3; ++d) x[d] = (a.seed_xyz[3 * p + d] - a.origin[d]) * a.g.inv_sp[d];
     int status = S_TERMINATED;
-    if (inside(a.g, x)) status = adj_steps<DT, MODE>(a, x, 0, a.N, a.tape ? a.tape + q : nullptr, a.ckpt != nullptr);
+    const TapeHook hook{a, a.tape ? a.tape + q : nullptr, a.ckpt ? a.ckpt + 3 * p : nullptr, 0};
+    if (inside(a.g, x)) status = adj_steps<DT, MODE>(a, x, 0, a.N, hook);
     a.status[p] = (uint8_t)status;
     a.bad[p] = 0;
 }
@@ -210,8 +308,8 @@ __global__ __launch_bounds__(ADJ_BLOCK) void adj_recompute_kernel(const AdjointA
     double x[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) x[d] = a.ckpt[a.ck_stride * (int64_t)sg + 3 * p + d];
-    TapeEntry* t = a.tape + 4 * a.np * (int64_t)(n0 - a.sg_last * a.k) + q;
-    if (adj_steps<DT, MODE>(a, x, n0, n1, t, false) != S_VALID) a.bad[p] = 1;
+    const TapeHook hook{a, a.tape + 4 * a.np * (int64_t)(n0 - a.sg_last * a.k) + q, nullptr, n0};
+    if (adj_steps<DT, MODE>(a, x, n0, n1, hook) != S_VALID) a.bad[p] = 1;
 }
 
 template <int DT, int MODE, int NCOT>
@@ -466,6 +564,14 @@ static unsigned adj_blocks(const AdjointArgs& a) { return (unsigned)((a.np + ADJ
 hipError_t launch_adj_forward(const AdjointArgs& a, int dtype, int mode, hipStream_t s) {
     return adj_dispatch(dtype, mode, [&](auto dt, auto md) {
         hipLaunchKernelGGL((adj_forward_kernel<decltype(dt)::value, decltype(md)::value>), dim3(adj_blocks(a)),
+                           dim3(ADJ_BLOCK), 0, s, a);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_adj_tangent(const AdjointArgs& a, int dtype, int mode, hipStream_t s) {
+    return adj_dispatch(dtype, mode, [&](auto dt, auto md) {
+        hipLaunchKernelGGL((adj_tangent_kernel<decltype(dt)::value, decltype(md)::value>), dim3(adj_blocks(a)),
                            dim3(ADJ_BLOCK), 0, s, a);
         return hipGetLastError();
     });

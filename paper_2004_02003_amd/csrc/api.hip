@@ -990,7 +990,9 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
     const size_t tab = (words * sizeof(uint64_t) + 255) & ~(size_t)255;
     // [tables | records per seed | status | bad | drop | checkpoints, unless they were recorded | tape]
     const size_t p4 = (P * sizeof(uint32_t) + 255) & ~(size_t)255, p1 = (P + 255) & ~(size_t)255;
-    const size_t ck = use_ck ? 0 : (P * 3 * sizeof(double) * (size_t)nseg + 255) & ~(size_t)255;
+    // the Jacobian is carried forward: no tape, no checkpoints
+    const bool tangent = !use_ck && n_cot == 3 && !d_grad_fields;
+    const size_t ck = use_ck || tangent ? 0 : (P * 3 * sizeof(double) * (size_t)nseg + 255) & ~(size_t)255;
     const size_t fixed = tab + p4 + 3 * p1 + ck;
     // The tape: as many whole segments as its budget holds, swept in groups; a
     // single segment beyond it is swept for a part of the seeds at a time.
@@ -1012,7 +1014,7 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
     };
     hipError_t e;
     size_t budget = ADJ_TAPE_BYTES;
-    plan(budget);
+    if (!tangent) plan(budget);
     if (fixed + tape > c->adj_bytes) {
         if (c->adj_scratch) {
             e = hipStreamSynchronize(s);
@@ -1026,7 +1028,7 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
             (void)hipGetLastError();
             c->adj_scratch = nullptr;
             const size_t had = tape;
-            while (budget > 0 && tape == had) plan(budget /= 2);
+            while (!tangent && budget > 0 && tape == had) plan(budget /= 2);
             if (tape == had) return fail(c, BTO_ENOMEM, "adjoint scratch of %zu bytes", fixed + tape);
         }
         c->adj_bytes = fixed + tape;
@@ -1074,6 +1076,12 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
     a.lam = lam ? lam : d_grad_seed;
     a.drop = drop ? drop : a.bad + p1;
     if (np < P || segs < nsg) a.nrec = nrec;
+    const int md = mode | wide_grids(c, dtype);
+    if (tangent) {
+        a.np = (int64_t)P;
+        e = launch_adj_tangent(a, dtype, md, s);
+        return e == hipSuccess ? BTO_OK : hip_fail(c, e, "adjoint launch");
+    }
     // grid gradients: records for the sorted reduction, unless the key does not fit
     a.grec = GradRec{};
     GradSort sort{};
@@ -1139,7 +1147,6 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
             }
         }
     }
-    const int md = mode | wide_grids(c, dtype);
     // the interval's own forward: straight onto the tape where it holds everything
     const bool whole = np == P && segs == nsg;
     if (!use_ck) {

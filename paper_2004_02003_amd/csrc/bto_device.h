@@ -834,14 +834,16 @@ __device__ __forceinline__ bool inside_flat(const Geom& g, const double p[3]) {
 //     conversions of f16 values folded into the FMAs (tile_gather_kernel, f16:
 //     1,411 vector instructions and 127 registers before, 982 and 91 now).
 // On entry A holds a cell of level n (or NO_CELL), B nothing; x is inside.
-// on_stage(s, c) is given the cell and the offsets that stage s samples.
+// on_stage(s, c) is given the cell and the offsets that stage s samples, and
+// on_sample(s, c) is called when A and B hold the corner values it used.
 // one_by_one (uniform): wait for level n before level n + 1 is asked for, as
 // rk4_step does -- two round trips, but half the lines in flight, which is the
 // better where the wavefronts' lines no longer fit the L1 (see the callers).
-template <int DT, int MODE, class OnExit, class OnStage = NoStage>
+template <int DT, int MODE, class OnExit, class OnStage = NoStage, class OnSample = NoStage>
 __device__ __forceinline__ int rk4_step_gather(const Geom& g, const char* V0, const char* V1, const StepSizes& hs,
                                                double* x, GatherCache<DT>& A, GatherCache<DT>& B, bool one_by_one,
-                                               OnExit&& on_exit, OnStage&& on_stage = OnStage{}) {
+                                               OnExit&& on_exit, OnStage&& on_stage = OnStage{},
+                                               OnSample&& on_sample = OnSample{}) {
     using R = SampleT<MODE>;
     constexpr bool W = is_wide<MODE>;
     int status = S_VALID;
@@ -869,6 +871,7 @@ __device__ __forceinline__ int rk4_step_gather(const Geom& g, const char* V0, co
     on_stage(0, c);
     if (A.val != c.val) A.template load<W>(g, V0, b);
     trilerp(A.rows(g), c.f, k);
+    on_sample(0, c);
 #pragma unroll
     for (int d = 0; d < 3; ++d) k1[d] = k[d];
     point(hs.half, k);
@@ -884,6 +887,7 @@ __device__ __forceinline__ int rk4_step_gather(const Geom& g, const char* V0, co
     } else {
         trilerp(A.rows(g), c.f, k);
     }
+    on_sample(1, c);
 #pragma unroll
     for (int d = 0; d < 3; ++d) k23[d] = k[d];
     point(hs.half, k);
@@ -903,6 +907,7 @@ __device__ __forceinline__ int rk4_step_gather(const Geom& g, const char* V0, co
     } else {
         trilerp(A.rows(g), c.f, k);
     }
+    on_sample(2, c);
 #pragma unroll
     for (int d = 0; d < 3; ++d) k23[d] = k23[d] + k[d];
     point(hs.full, k);
@@ -917,6 +922,7 @@ __device__ __forceinline__ int rk4_step_gather(const Geom& g, const char* V0, co
         if (A.val != c.val) A.template load<W>(g, V0, b);
         trilerp(A.rows(g), c.f, k);
     }
+    on_sample(3, c);
     R ks[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) ks[d] = (k1[d] + k[d]) + (R)2 * k23[d];

@@ -102,3 +102,36 @@ def test_grid_gradient_reduction_at_its_sizes(n, N, P, monkeypatch):
     for x, y in zip(a, c):
         assert float((x - y).abs().max()) <= 2e-5 * top
         assert torch.equal(x != 0, y != 0)
+
+
+@pytest.mark.parametrize("mode", ["linear", "frozen"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("P", [1, 65, 3000])
+def test_tangent_sweep_equals_the_reverse_sweep(P, dtype, mode):
+    """Three cotangents: carried forward from the seeds, and backwards from
+    recorded checkpoints.  Two orders of the same FP32 products: N steps of
+    four stages with eight roundings each, relative to the gradients' norm."""
+    from paper_2004_02003_amd import Context
+
+    n, N = (30, 21, 26), 13
+    g = torch.Generator(device="cuda").manual_seed(P)
+    grids = [(0.4 * torch.randn((n[2], n[1], n[0], 3), device="cuda", generator=g)).to(dtype) for _ in range(N + 1)]
+    times = np.arange(N + 1) * 0.1
+    hi = torch.tensor([v - 1.0 for v in n], dtype=torch.float64, device="cuda")
+    sp = torch.tensor([0.5, 1.0, 0.25], dtype=torch.float64, device="cuda")
+    seeds = (torch.rand((P, 3), dtype=torch.float64, device="cuda", generator=g) * 0.96 + 0.02) * hi * sp
+    seeds[1::17] -= 100.0  # outside from the start
+    cot = torch.randn((P, 3, 3), device="cuda", generator=g)
+    print(f"[gpu-case] tangent {P} {dtype} {mode}", file=sys.stderr, flush=True)
+    with Context(n, P, spacing=sp.tolist()) as ctx:
+        ctx.set_tuning(ckpt_every=N, steps_per_launch=N)  # one launch: the recorded forward is the recomputed one
+        st = [torch.empty(P, dtype=torch.uint8, device="cuda") for _ in range(2)]
+        ctx.seed_explicit(seeds)
+        ctx.advect(grids, times, mode=mode, record_ckpt=True)
+        a = ctx.adjoint(grids, times, cot, ckpt_every=N, mode=mode, status=st[0], recorded=True)
+        b = ctx.adjoint(grids, times, cot, ckpt_every=N, mode=mode, status=st[1])
+        torch.cuda.synchronize()
+    assert torch.equal(st[0], st[1])
+    assert torch.equal(b[st[1] != 0], torch.zeros_like(b[st[1] != 0]))
+    assert P < 100 or (st[1] == 1).any()
+    assert float((a - b).norm()) <= N * 32 * 2.0 ** -24 * float(a.norm())
