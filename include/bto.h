@@ -191,8 +191,9 @@ int bto_stats(bto_ctx *ctx, bto_stats_t *out, void *stream);
  *   rebin_every         re-sort the live particles by 32x2x2-cell bin, bins in
  *                       x-fastest order, every this many steps (restores cache
  *                       locality as the flow mixes them; 0 = never, the default);
- *   blocks_per_cu       cap on resident advection workgroups per compute unit
- *                       (0 = as many as the register budget allows);
+ *   blocks_per_cu       cap on the advection workgroups per compute unit, which
+ *                       then loop over the particles (0: a workgroup per 256
+ *                       particles);
  *   lanes_per_particle  1 (default) or 2.  With 2 and FP32 storage, the two
  *                       lanes of a pair each load and weight one x-corner of
  *                       every cell row and add their partial sums; this halves

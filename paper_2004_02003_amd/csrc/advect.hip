@@ -180,10 +180,14 @@ static auto with_variant(int dtype, int mode, int lpp, int rec, F&& f) {
     }
 }
 
-hipError_t launch_advect(const AdvectArgs& a, int dtype, int mode, int lpp, int rec, int R, hipStream_t s) {
+// Unused LDS of which two workgroups, but not three, find room on a CU (160 KB).
+constexpr unsigned PAIR_LDS = 56 * 1024;
+
+hipError_t launch_advect(const AdvectArgs& a, int dtype, int mode, int lpp, int rec, int R, bool pair, hipStream_t s) {
     return with_variant(dtype, mode, lpp, rec, [&](auto v) {
         using V = decltype(v);
-        hipLaunchKernelGGL((advect_kernel<V::DT, V::MODE, V::LPP, V::REC>), dim3(R * NSEG), dim3(BLOCK), 0, s, a);
+        hipLaunchKernelGGL((advect_kernel<V::DT, V::MODE, V::LPP, V::REC>), dim3(R * NSEG), dim3(BLOCK),
+                           pair ? PAIR_LDS : 0u, s, a);
         return hipGetLastError();
     });
 }

@@ -134,11 +134,13 @@ static void set_segments(bto_ctx* c, int64_t P) {
     for (int x = 0; x < NSEG; ++x) c->seg_cap[x] = (x + 1 < NSEG ? c->segs.base[x + 1] : P) - c->segs.base[x];
 }
 
+// Workgroups per segment, one batch of particles each; per_cu > 0: at most that
+// many per CU, which then loop over the batches.
 static int blocks_per_seg(const bto_ctx* c, int64_t max_seg, int per_cu) {
     int64_t need = (max_seg + BLOCK - 1) / BLOCK;
-    int64_t lim = (int64_t)c->cus_per_xcd * per_cu;
+    const int64_t lim = (int64_t)c->cus_per_xcd * per_cu;
     if (need < 1) need = 1;
-    return (int)(need < lim ? need : lim);
+    return (int)(per_cu > 0 && lim < need ? lim : need);
 }
 
 extern "C" {
@@ -737,7 +739,7 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
             return fail(c, BTO_EINVAL, "this interval's tile layout has %d-cell tiles; storage type %d needs %d",
                         c->tg.T[0], dtype, tile_side(dtype, c->tiles == 1, 0));
         if (!c->tile_layout) {
-            rc = tile_enter(c, dtype, blocks_per_seg(c, max_seg, 4), s);
+            rc = tile_enter(c, dtype, blocks_per_seg(c, max_seg, 0), s);
             if (rc) return rc;
         }
         for (int32_t q = 0; q < n_steps; ++q) {
@@ -751,9 +753,32 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
         return BTO_OK;
     }
     const int lpp = dtype == BTO_F32 ? c->lanes_per_particle : 1;
-    int per_cu = advect_max_blocks_per_cu(dtype, mode, lpp, rec);
-    if (c->blocks_per_cu_cap > 0 && c->blocks_per_cu_cap < per_cu) per_cu = c->blocks_per_cu_cap;
+    // A workgroup takes one batch and leaves, unless the tuning caps the
+    // workgroups per CU.  Loops over batches in a grid that fills the chip once
+    // (4 or 5 workgroups per CU) took, for 20 steps of a 256^3 turbulence block
+    // with 2 million particles, 4.54 ms instead of 3.20 (f16) and 6.84 instead of
+    // 5.03 (f32) in launches of 1 step, 3.41 instead of 2.70 and 4.60 instead of
+    // 3.93 in launches of 5; a 128^3 ABC block fits the chip at once (0.83, 0.82).
+    int per_cu = 0;
+    if (c->blocks_per_cu_cap > 0) {
+        per_cu = advect_max_blocks_per_cu(dtype, mode, lpp, rec);
+        if (c->blocks_per_cu_cap < per_cu) per_cu = c->blocks_per_cu_cap;
+    }
     const int R = blocks_per_seg(c, max_seg * lpp, per_cu);
+    // Particles far apart (less than one per four cells) share few lines, and
+    // those of four or five workgroups do not stay in a CU's L1 from one step of
+    // a launch to the next: two at a time do (LDS they do not use keeps the
+    // others out).  The blocks above: launches of 5 steps 2.49 ms instead of 2.70
+    // (f16) and 3.63 instead of 3.93 (f32), of 20 steps 2.46 instead of 3.31 and
+    // 3.60 instead of 4.27.  Launches of 2 or 3 steps gain less or lose (f16: 2.85
+    // instead of 2.74), as does a block with a particle in every cell (bf16, 200 x
+    // 180 x 150, 5 steps: 2.34 instead of 2.07).  Where the chip holds every
+    // workgroup at once anyway, two rounds of two pay off later (128^3 ABC, 4 per
+    // CU: 5 steps 0.47 instead of 0.46, 25 steps 0.676 instead of 0.700; 160^3
+    // turbulence with FP64 sampling, 8 per CU: 5 steps 0.92 instead of 0.96).
+    const int64_t cells = (int64_t)(c->blk.n[0] - 1) * (c->blk.n[1] - 1) * (c->blk.n[2] - 1);
+    const bool sparse = 4 * c->n_seeds <= cells && lpp == 1 && per_cu == 0;
+    const int pair_from = R >= 6 * c->cus_per_xcd ? 4 : 8;
     // launches of (nearly) equal length, at most steps_per_launch steps each
     int kmax = c->steps_per_launch;
     if (c->rebin_every > 0 && c->rebin_every < kmax) kmax = c->rebin_every;
@@ -778,7 +803,7 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
             ca.pos = c->pos[c->cur];
             ca.id = c->id[c->cur];
             ca.out = c->ck_rec + (size_t)(c->steps_done / c->ck_k) * (size_t)c->cap * 3;
-            hipError_t e = launch_ckpt_store(ca, blocks_per_seg(c, max_seg, 4), s);
+            hipError_t e = launch_ckpt_store(ca, blocks_per_seg(c, max_seg, 0), s);
             if (e != hipSuccess) return hip_fail(c, e, "checkpoint store launch");
         }
         AdvectArgs a{};
@@ -799,7 +824,7 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
         a.rec_meta = c->rec_meta;
         a.rec_out = c->rec_out;
         a.psteps = c->psteps;
-        hipError_t e = launch_advect(a, dtype, mode, lpp, rec, R, s);
+        hipError_t e = launch_advect(a, dtype, mode, lpp, rec, R, sparse && K >= pair_from, s);
         if (e != hipSuccess) return hip_fail(c, e, "advect launch");
         c->cur = 1 - c->cur;
         c->slot = (c->slot + 1) % 3;
@@ -840,7 +865,7 @@ int bto_flowmap_out(bto_ctx* c, double* d_seed_xyz, double* d_end_xyz, uint8_t* 
         int64_t max_seg = 0;
         for (int x = 0; x < NSEG; ++x) max_seg = c->seg_cap[x] > max_seg ? c->seg_cap[x] : max_seg;
         // the segment writer only when the live particles are in the segments
-        hipError_t e = launch_flowmap(a, c->tile_layout ? 0 : blocks_per_seg(c, max_seg, 4), s);
+        hipError_t e = launch_flowmap(a, c->tile_layout ? 0 : blocks_per_seg(c, max_seg, 0), s);
         if (e != hipSuccess) return hip_fail(c, e, "flowmap launch");
         if (c->tile_layout) {
             rc = tile_live(c, d_end_xyz, nullptr, s);

@@ -341,8 +341,9 @@ hipError_t launch_seed_lattice(const SeedLatticeArgs& a, hipStream_t s);
 hipError_t launch_seed_explicit(const SeedExplicitArgs& a, hipStream_t s);
 hipError_t launch_set_counts(uint32_t* counts, const uint32_t* values, int n, unsigned long long* psteps,
                              hipStream_t s);
+// pair: at most two workgroups on a CU at a time.
 hipError_t launch_advect(const AdvectArgs& a, int dtype, int mode, int lanes_per_particle, int record_exit,
-                         int blocks_per_seg, hipStream_t s);
+                         int blocks_per_seg, bool pair, hipStream_t s);
 hipError_t launch_exit_points(const FlowmapArgs& a, hipStream_t s);
 hipError_t launch_reconstruct(const int32_t m[3], double* end, const uint8_t* flag, uint8_t* state, hipStream_t s);
 size_t err_scratch_bytes(int64_t P);
