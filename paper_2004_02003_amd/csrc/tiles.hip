@@ -640,10 +640,16 @@ __global__ __launch_bounds__(BLOCK) void tile_live_kernel(const TileLiveArgs a) 
 // ---------------------------------------------------------------------------
 // Launchers.
 // ---------------------------------------------------------------------------
+// Unused LDS of which four workgroups, but not five, find room on a CU (160 KB)
+// beside their own.  FP32 cells take twice the lines of 16-bit ones, and the
+// lines of four workgroups stay longer in the L1: 167 -> 165 us per step of a
+// 256^3 turbulence block with 2 million particles; f16 loses (107 -> 108).
+constexpr unsigned FOUR_LDS = 30 * 1024;
+
 template <int DT, int MODE, int REC>
 static hipError_t launch_tile_step_t(const TileStepArgs& a, int list_blocks, hipStream_t s) {
     hipLaunchKernelGGL((tile_gather_kernel<DT, MODE, REC, GATHER_NT>), dim3(a.order_len + list_blocks), dim3(GATHER_NT),
-                       0, s, a);
+                       DT == DT_F32 ? FOUR_LDS : 0u, s, a);
     return hipGetLastError();
 }
 
