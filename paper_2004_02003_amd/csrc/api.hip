@@ -769,16 +769,18 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
     // those of four or five workgroups do not stay in a CU's L1 from one step of
     // a launch to the next: two at a time do (LDS they do not use keeps the
     // others out).  The blocks above: launches of 5 steps 2.49 ms instead of 2.70
-    // (f16) and 3.63 instead of 3.93 (f32), of 20 steps 2.46 instead of 3.31 and
-    // 3.60 instead of 4.27.  Launches of 2 or 3 steps gain less or lose (f16: 2.85
-    // instead of 2.74), as does a block with a particle in every cell (bf16, 200 x
-    // 180 x 150, 5 steps: 2.34 instead of 2.07).  Where the chip holds every
+    // (f16), 3.63 instead of 3.93 (f32) and 3.35 instead of 3.63 (f32, two lanes),
+    // of 20 steps 2.46 instead of 3.31, 3.60 instead of 4.27 and 3.12 instead of
+    // 4.23.  FP32 cells, twice the lines, gain from launches of 2 steps on (4.00
+    // instead of 4.13); the others lose there (f16 2.85 instead of 2.74, two lanes
+    // 4.05 instead of 3.56), as does a block with a particle in every cell (bf16,
+    // 200 x 180 x 150, 5 steps: 2.34 instead of 2.07).  Where the chip holds every
     // workgroup at once anyway, two rounds of two pay off later (128^3 ABC, 4 per
     // CU: 5 steps 0.47 instead of 0.46, 25 steps 0.676 instead of 0.700; 160^3
     // turbulence with FP64 sampling, 8 per CU: 5 steps 0.92 instead of 0.96).
     const int64_t cells = (int64_t)(c->blk.n[0] - 1) * (c->blk.n[1] - 1) * (c->blk.n[2] - 1);
-    const bool sparse = 4 * c->n_seeds <= cells && lpp == 1 && per_cu == 0;
-    const int pair_from = R >= 6 * c->cus_per_xcd ? 4 : 8;
+    const bool sparse = 4 * c->n_seeds <= cells && per_cu == 0;
+    const int pair_from = R < 6 * c->cus_per_xcd ? 8 : dtype == BTO_F32 && lpp == 1 ? 2 : 4;
     // launches of (nearly) equal length, at most steps_per_launch steps each
     int kmax = c->steps_per_launch;
     if (c->rebin_every > 0 && c->rebin_every < kmax) kmax = c->rebin_every;
