@@ -765,22 +765,25 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
         if (c->blocks_per_cu_cap < per_cu) per_cu = c->blocks_per_cu_cap;
     }
     const int R = blocks_per_seg(c, max_seg * lpp, per_cu);
-    // Particles far apart (less than one per four cells) share few lines, and
+    // FP32 particles far apart (less than one per four cells) share few lines, and
     // those of four or five workgroups do not stay in a CU's L1 from one step of
     // a launch to the next: two at a time do (LDS they do not use keeps the
-    // others out).  The blocks above: launches of 5 steps 2.49 ms instead of 2.70
-    // (f16), 3.63 instead of 3.93 (f32) and 3.35 instead of 3.63 (f32, two lanes),
-    // of 20 steps 2.46 instead of 3.31, 3.60 instead of 4.27 and 3.12 instead of
-    // 4.23.  FP32 cells, twice the lines, gain from launches of 2 steps on (4.00
-    // instead of 4.13); the others lose there (f16 2.85 instead of 2.74, two lanes
-    // 4.05 instead of 3.56), as does a block with a particle in every cell (bf16,
-    // 200 x 180 x 150, 5 steps: 2.34 instead of 2.07).  Where the chip holds every
-    // workgroup at once anyway, two rounds of two pay off later (128^3 ABC, 4 per
-    // CU: 5 steps 0.47 instead of 0.46, 25 steps 0.676 instead of 0.700; 160^3
-    // turbulence with FP64 sampling, 8 per CU: 5 steps 0.92 instead of 0.96).
+    // others out).  The f32 block above: launches of 2 steps 4.00 ms instead of
+    // 4.13, of 5 steps 3.63 instead of 3.93 (re-sorted after each: 3.99 instead of
+    // 4.20 for 25 steps), of 20 steps 3.60 instead of 4.27; one step 5.00 instead
+    // of 5.03.  Where the chip holds every workgroup at once anyway, two rounds of
+    // two pay off later (128^3 ABC, 4 per CU: 5 steps 0.47 instead of 0.46, 25
+    // steps 0.676 instead of 0.700).  It does not pay with a particle in every
+    // cell (200 x 180 x 150, 5 steps: 2.34 instead of 2.07, bf16); for 16-bit
+    // grids, whose lines hold twice the cells (200^3 ABC, f16: 0.93 instead of
+    // 0.69); for one level per step (200 x 190 x 180 ABC, frozen: 0.86 instead of
+    // 0.83); with FP64 sampling, whose chains are longer (180^3 ABC: 1.00 instead
+    // of 0.94); nor for two lanes per particle (the f32 block re-sorted every 5
+    // steps: 3.88 instead of 3.68).
     const int64_t cells = (int64_t)(c->blk.n[0] - 1) * (c->blk.n[1] - 1) * (c->blk.n[2] - 1);
-    const bool sparse = 4 * c->n_seeds <= cells && per_cu == 0;
-    const int pair_from = R < 6 * c->cus_per_xcd ? 8 : dtype == BTO_F32 && lpp == 1 ? 2 : 4;
+    const bool may_pair = dtype == BTO_F32 && (mode & ~MODE_WIDE) == MODE_LINEAR && lpp == 1 && per_cu == 0 &&
+                          4 * c->n_seeds <= cells;
+    const int pair_from = R >= 6 * c->cus_per_xcd ? 2 : 8;
     // launches of (nearly) equal length, at most steps_per_launch steps each
     int kmax = c->steps_per_launch;
     if (c->rebin_every > 0 && c->rebin_every < kmax) kmax = c->rebin_every;
@@ -826,7 +829,7 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
         a.rec_meta = c->rec_meta;
         a.rec_out = c->rec_out;
         a.psteps = c->psteps;
-        hipError_t e = launch_advect(a, dtype, mode, lpp, rec, R, sparse && K >= pair_from, s);
+        hipError_t e = launch_advect(a, dtype, mode, lpp, rec, R, may_pair && K >= pair_from, s);
         if (e != hipSuccess) return hip_fail(c, e, "advect launch");
         c->cur = 1 - c->cur;
         c->slot = (c->slot + 1) % 3;
