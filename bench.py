@@ -697,8 +697,8 @@ def turb_storage_legs(log, copy_gbs, steps=3, warmup=1):
                    "interval_ms": round(m["interval_ms_median"], 4), "particle_steps": m["particle_steps"],
                    "valid_at_end": m["valid_at_end"],
                    "roofline": roofline_of(m, dt, wl.name, "insitu_fp64" if fp64 else "insitu",
-                                           f"tile_gather_kernel<{dt},linear{',extended-precision sampling' if fp64 else ''}> + "
-                                           f"tile_list_kernel (one step per call)", copy_gbs),
+                                           f"tile_gather_kernel<{dt},linear{',extended-precision sampling' if fp64 else ''}> "
+                                           f"(one step per call)", copy_gbs),
                    "tuning": m["tuning"]}
             # fused: all grids resident, several steps per launch (segment layout,
             # latched at the next seeding)
@@ -965,7 +965,7 @@ def main(argv=None):
     torch.cuda.empty_cache()
     value = m["particle_steps"] / (m["interval_ms_median"] * 1e-3)
     copy_gbs = device_copy_rate()
-    kname = (f"tile_gather_kernel<{dt},linear> + tile_list_kernel (one step per call)" if m["tuning"].get("tiles")
+    kname = (f"tile_gather_kernel<{dt},linear> (one step per call)" if m["tuning"].get("tiles")
              else f"advect_kernel<{dt},linear> (one step per call)")
     roof = roofline_of(m, dt, wl.name, "insitu", kname, copy_gbs)
     result = {

@@ -204,8 +204,9 @@ int bto_stats(bto_ctx *ctx, bto_stats_t *out, void *stream);
  *   ckpt_every          steps between the checkpoints that BTO_RECORD_CKPT
  *                       records (>= 1, default 10);
  *   tiles               0 (default), 1 or 2.  With 1 or 2, every RK4 step is
- *                       its own pair of launches over the live particles kept
- *                       in buckets by tile of cells, one workgroup per tile,
+ *                       a launch of its own over the live particles kept in
+ *                       buckets by tile of cells (with 1, a second one for
+ *                       what the first left), one workgroup per tile,
  *                       tiles along a Hilbert curve in cell space with one
  *                       eighth of them per XCD; each survivor goes into the bucket of the tile it
  *                       ends in, so the particles stay sorted by tile.  With 2

@@ -1,5 +1,5 @@
 """The advection's launch shapes -- a workgroup per 256 particles, two on a CU
-at a time (sparse particles, launches of 2, 4 or 8 steps on), or a capped number
+at a time (sparse FP32 particles, launches of 2 or 8 steps on), or a capped number
 that loops -- move the same particles by the same bits."""
 
 import sys
@@ -21,7 +21,7 @@ def _need_gpu():
 
 
 # per segment (an eighth of the particles): under a workgroup, a few, and more
-# than 6 x 32 (from where launches of 4 steps go in pairs)
+# than 6 x 32 (from where launches of 2 steps go in pairs)
 @pytest.mark.parametrize("P,n", [(5, (40, 30, 20)), (2049, (9, 8, 7)), (2047, (40, 30, 20)), (420_001, (130, 121, 119))])
 @pytest.mark.parametrize("K", [1, 2, 4, 9])
 @pytest.mark.parametrize("dtype,fp64,lanes", [(torch.float32, False, 1), (torch.float16, False, 1),
