@@ -386,7 +386,10 @@ int bto_reconstruct_lattice(const int32_t m[3], double *d_end_xyz, const uint8_t
  * L2 norm), out5[1] = maximum |b - m|, out5[2] = entries compared, out5[3] =
  * entries m keeps that b leaves missing, out5[4] = (cell - mean) / cell * 100
  * (Accuracy%, cell = the grid cell side in the same units).  out5 is host
- * memory; synchronizes `stream`.  Deterministic for a given n. */
+ * memory; synchronizes `stream`.  Deterministic for a given n.  The process
+ * keeps scratch for up to eight calls at a time (32 KB of device memory and a
+ * pinned record each, made when first needed); further calls at the same time
+ * allocate theirs and free it. */
 int bto_flowmap_error(int64_t n, const double *d_b_xyz, const uint8_t *d_b_state, const double *d_m_xyz,
                       const uint8_t *d_m_flag, double cell, double *out5, void *stream);
 
