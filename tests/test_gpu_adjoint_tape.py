@@ -135,3 +135,45 @@ def test_tangent_sweep_equals_the_reverse_sweep(P, dtype, mode):
     assert torch.equal(b[st[1] != 0], torch.zeros_like(b[st[1] != 0]))
     assert P < 100 or (st[1] == 1).any()
     assert float((a - b).norm()) <= N * 32 * 2.0 ** -24 * float(a.norm())
+
+
+@pytest.mark.parametrize("dtype,n", [(torch.float16, (1024, 1023, 701)), (torch.float32, (1024, 701, 513))])
+def test_adjoint_on_grids_beyond_4_gib(dtype, n):
+    """A flow that lives in the last 60 x 50 x 40 points of a grid beyond 4 GiB
+    (zero elsewhere, so a wrong address shows) against the same flow on a grid
+    of those points alone: Jacobians (carried forward) and seed gradients
+    (reverse sweep).  The same FP32 arithmetic on FP64 positions shifted by
+    whole cells: offsets to 2^-24, four stages of two steps."""
+    from paper_2004_02003_amd import Context
+
+    g = torch.Generator(device="cuda").manual_seed(2)
+    m = (60, 50, 40)
+    big, small = [], []
+    for _ in range(3):
+        s = (0.3 * torch.randn((m[2], m[1], m[0], 3), device="cuda", generator=g)).to(dtype)
+        b = torch.zeros((n[2], n[1], n[0], 3), dtype=dtype, device="cuda")
+        assert b.numel() * b.element_size() > 1 << 32
+        b[-m[2]:, -m[1]:, -m[0]:] = s
+        big.append(b)
+        small.append(s)
+    P = 3000
+    off = torch.tensor([a - b for a, b in zip(n, m)], dtype=torch.float64, device="cuda")
+    hi = torch.tensor([v - 1.0 for v in m], dtype=torch.float64, device="cuda")
+    x0 = 3.0 + torch.rand((P, 3), dtype=torch.float64, device="cuda", generator=g) * (hi - 4.0)  # up to the last cells
+    cot = torch.randn((P, 3, 3), device="cuda", generator=g)
+    out = []
+    print(f"[gpu-case] adjoint beyond 4 GiB {dtype} {n}", file=sys.stderr, flush=True)
+    for size, grids, seeds in ((n, big, x0 + off), (m, small, x0)):
+        with Context(size, P) as ctx:
+            ctx.seed_explicit(seeds.contiguous())
+            st = torch.empty(P, dtype=torch.uint8, device="cuda")
+            j = ctx.adjoint(grids, [0.0, 0.5, 1.0], cot, ckpt_every=2, status=st)
+            r = ctx.adjoint(grids, [0.0, 0.5, 1.0], cot[:, :1].contiguous(), ckpt_every=2)
+            torch.cuda.synchronize()
+            out.append((st.cpu(), j.cpu(), r.cpu()))
+    (sb, jb, rb), (ss, js, rs) = out
+    assert int((ss == 0).sum()) > P // 2
+    ok = (sb == 0) & (ss == 0)
+    assert int((sb != ss).sum()) <= 2  # an end point within rounding of a face
+    for a, b in ((jb, js), (rb, rs)):
+        assert float((a[ok] - b[ok]).norm()) <= 2 * 32 * 2.0 ** -24 * 4 * float(b[ok].norm())
