@@ -33,14 +33,16 @@ __device__ __forceinline__ T* in_global(T* p) {
     return (T*)(G)(uintptr_t)p;
 }
 
-// A value that is the same in every lane, moved to scalar registers (in
-// assembly: the compiler drops its own builtin where it knows the value to be
-// uniform, and keeps it in vector registers all the same).
+// A value that is the same in every lane, moved to scalar registers.  Its words
+// are made opaque first: the compiler drops its own builtin where it knows the
+// value to be uniform, and keeps it in vector registers all the same.  The move
+// itself is the builtin and not assembly, because gfx950 wants wait states
+// between the vector write of a register and v_readfirstlane's read of it, and
+// behind it, which the compiler puts in only for instructions that it sees.
 __device__ __forceinline__ double uniform(double v) {
     const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    uint32_t lo, hi;
-    asm("v_readfirstlane_b32 %0, %1" : "=s"(lo) : "v"((uint32_t)b));
-    asm("v_readfirstlane_b32 %0, %1" : "=s"(hi) : "v"((uint32_t)(b >> 32)));
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)opaque((uint32_t)b));
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)opaque((uint32_t)(b >> 32)));
     return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
