@@ -60,7 +60,7 @@ __device__ __forceinline__ void gT(const float G[3][3], const float v[3], float 
 struct GradAcc {
     uint32_t val;   // cell (first value's index; NO_CELL: none)
     int level;
-    uint32_t nrec;  // records written by this seed
+    uint32_t nrec;  // records written by this seed (per_seed + 1: and then flushes added with atomics)
     float v[8][3];
 };
 
@@ -90,6 +90,7 @@ __device__ __forceinline__ void acc_flush(const Geom& g, float* const* gf, const
         A.val = NO_CELL;
         return;
     }
+    if (R.key) A.nrec = R.per_seed + 1u;
     float* grid = in_global(gf[A.level]) + A.val;
 #pragma unroll
     for (int c = 0; c < 2; ++c)
