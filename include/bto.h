@@ -253,7 +253,8 @@ int bto_get_tuning(const bto_ctx *ctx, bto_tuning *t);
  * of RK4 with the trilinear sampler's gradient on the cell chosen by the
  * floor/clamp rule.  An interval whose stages pass 1 GiB (64 bytes per step
  * and seed) is swept in groups of segments of ckpt_every steps, each
- * recomputed from the positions at its first step.  With n_cot = 3, no grid
+ * recomputed from the positions at its first step; the grid gradients are the
+ * same bits however many groups there are.  With n_cot = 3, no grid
  * gradients and no recorded checkpoints the same derivatives are carried along
  * the forward steps instead (one sweep, nothing kept).
  *   d_cot_end  (n_seeds x n_cot x 3 floats, world units): cotangents of the
@@ -287,9 +288,12 @@ int bto_get_tuning(const bto_ctx *ctx, bto_tuning *t);
  * the recorded flags.
  * Seeds that do not stay inside the block for the whole interval contribute
  * nothing: their gradient rows are zero.  Scratch of up to 1 GiB for the
- * stages (less where that much memory is not free) and about
- * n_seeds * n_steps / ckpt_every * 24 bytes for the positions is held by the
- * context, grown on demand (a growth synchronizes `stream`). */
+ * stages (less where that much memory is not free), about
+ * n_seeds * n_steps / ckpt_every * 24 bytes for the positions and, for grid
+ * gradients in several groups, 108 bytes per seed for the sums carried from one
+ * to the next (a card without room for these sums gets them flushed by each
+ * group, which then shows in the last bits) is held by the context, grown on
+ * demand (a growth synchronizes `stream`). */
 int bto_adjoint_interval(bto_ctx *ctx, const void *const *d_fields, const double *times, int32_t n_steps,
                          int32_t dtype, int32_t flags, const float *d_cot_end, int32_t n_cot, float *d_grad_seed,
                          float *const *d_grad_fields, uint8_t *d_status, int32_t ckpt_every, void *stream);

@@ -51,7 +51,8 @@ __device__ __forceinline__ void gT(const float G[3][3], const float v[3], float 
 // Grid-gradient accumulator: the 8 corner gradients of one cell of one grid
 // level, summed in registers while consecutive stage contributions hit the
 // same cell and level, and flushed only when the cell or level changes (and at
-// the end of each launch).  In the reverse sweep a level receives
+// the end of each call; between the launches of a call it is kept in memory, so
+// that the sums do not depend on how many the tape needs).  In the reverse sweep a level receives
 // its contributions from two consecutive steps (level n from step n's first
 // three stages and from step n-1's last three), so a particle that stays in
 // its cell flushes once per level.  A flush appends a record for the sorted,
@@ -63,6 +64,22 @@ struct GradAcc {
     uint32_t nrec;  // records written by this seed (per_seed + 1: and then flushes added with atomics)
     float v[8][3];
 };
+
+// The accumulator of seed p between two launches: words 1 .. 26 of its ACC_WORDS
+// (word 0: nrec), a word of all P seeds side by side.
+__device__ __forceinline__ void acc_load(const uint32_t* w, int64_t P, int64_t p, GradAcc& A) {
+    A.val = w[P + p];
+    A.level = (int)w[2 * P + p];
+#pragma unroll
+    for (int j = 0; j < 24; ++j) A.v[j / 3][j % 3] = __uint_as_float(w[(3 + j) * P + p]);
+}
+
+__device__ __forceinline__ void acc_store(uint32_t* w, int64_t P, int64_t p, const GradAcc& A) {
+    w[P + p] = A.val;
+    w[2 * P + p] = (uint32_t)A.level;
+#pragma unroll
+    for (int j = 0; j < 24; ++j) w[(3 + j) * P + p] = __float_as_uint(A.v[j / 3][j % 3]);
+}
 
 __device__ __forceinline__ void put_key(const GradRec& R, uint64_t slot, uint64_t key) {
     if (R.key_bytes == 4) static_cast<uint32_t*>(R.key)[slot] = (uint32_t)key;
@@ -339,8 +356,12 @@ __global__ __launch_bounds__(ADJ_BLOCK) void adj_reverse_kernel(const AdjointArg
     GradAcc acc;
     acc.val = NO_CELL;
     acc.level = -1;
-    acc.nrec = a.nrec && a.sg_first != a.call_first ? a.nrec[p] : 0u;
+    acc.nrec = 0u;
+    // what the call's launch before this one left, and what this one leaves
+    const bool resumes = a.carry && a.sg_first != a.call_first, leaves = a.carry && a.sg_last != a.call_last;
+    if (resumes) acc.nrec = a.carry[p];
     if (on) {
+        if (resumes && a.carry_acc) acc_load(a.carry, a.P, p, acc);
         const TapeEntry* t = a.tape + q;
         const auto read = [&](int n, TapeEntry* e) {
 #pragma unroll
@@ -452,7 +473,8 @@ __global__ __launch_bounds__(ADJ_BLOCK) void adj_reverse_kernel(const AdjointArg
                 e[s] = e2[s];
             }
         }
-        if (a.grad_f) acc_flush(a.g, a.grad_f, a.grec, (uint32_t)p, acc);
+        if (leaves && a.carry_acc) acc_store(a.carry, a.P, p, acc);
+        else if (a.grad_f) acc_flush(a.g, a.grad_f, a.grec, (uint32_t)p, acc);
     }
     int drop = prior;
     if (bad) {
@@ -475,7 +497,7 @@ __global__ __launch_bounds__(ADJ_BLOCK) void adj_reverse_kernel(const AdjointArg
         drop = withdrawn ? ADJ_DROPPED : ADJ_DROPPED_PARTIAL;
     }
     if (a.drop && (first || drop != prior)) a.drop[p] = (uint8_t)drop;
-    if (a.nrec && !last) a.nrec[p] = acc.nrec;
+    if (leaves) a.carry[p] = acc.nrec;
     if (last) {
         if (a.status_out) a.status_out[p] = (uint8_t)(drop ? drop : status);
 #pragma unroll

@@ -1018,16 +1018,17 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
     const size_t nsg = (size_t)(sg_first - sg_last + 1);
     const size_t words = (size_t)(n_local + 1) * 2 + (size_t)n_local;
     const size_t tab = (words * sizeof(uint64_t) + 255) & ~(size_t)255;
-    // [tables | records per seed | status | bad | drop | checkpoints, unless they were recorded | tape]
-    const size_t p4 = (P * sizeof(uint32_t) + 255) & ~(size_t)255, p1 = (P + 255) & ~(size_t)255;
+    // [tables | status | bad | drop | checkpoints, unless they were recorded | carried per seed | tape]
+    const size_t p1 = (P + 255) & ~(size_t)255;
     // the Jacobian is carried forward: no tape, no checkpoints
     const bool tangent = !use_ck && n_cot == 3 && !d_grad_fields;
     const size_t ck = use_ck || tangent ? 0 : (P * 3 * sizeof(double) * (size_t)nseg + 255) & ~(size_t)255;
-    const size_t fixed = tab + p4 + 3 * p1 + ck;
+    const size_t fixed = tab + 3 * p1 + ck;
     // The tape: as many whole segments as its budget holds, swept in groups; a
-    // single segment beyond it is swept for a part of the seeds at a time.
+    // single segment beyond it is swept for a part of the seeds at a time.  With
+    // several groups, the gradient sums go from one to the next in memory.
     const size_t per = (size_t)K * 4 * sizeof(TapeEntry);
-    size_t np = 0, segs = 0, tape = 0;
+    size_t np = 0, segs = 0, tape = 0, carry = 0, carry_words = ACC_WORDS;
     const auto plan = [&](size_t budget) {
         np = P;
         segs = budget / (P * per);
@@ -1041,11 +1042,12 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
         segs = segs < 32768 ? segs : 32768;
         const size_t steps = segs * (size_t)K < (size_t)n_local ? segs * (size_t)K : (size_t)n_local;
         tape = np * steps * 4 * sizeof(TapeEntry);
+        carry = d_grad_fields && segs < nsg ? (P * carry_words * sizeof(uint32_t) + 255) & ~(size_t)255 : 0;
     };
     hipError_t e;
     size_t budget = ADJ_TAPE_BYTES;
     if (!tangent) plan(budget);
-    if (fixed + tape > c->adj_bytes) {
+    if (fixed + carry + tape > c->adj_bytes) {
         if (c->adj_scratch) {
             e = hipStreamSynchronize(s);
             if (e != hipSuccess) return hip_fail(c, e, "adjoint scratch sync");
@@ -1053,15 +1055,20 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
             c->adj_scratch = nullptr;
             c->adj_bytes = 0;
         }
-        // a card without that much memory left gets by with a shorter tape
-        while (hipMalloc(&c->adj_scratch, fixed + tape) != hipSuccess) {
+        // a card without that much memory left gets by with a shorter tape, and in
+        // the end with sums that each group flushes
+        while (hipMalloc(&c->adj_scratch, fixed + carry + tape) != hipSuccess) {
             (void)hipGetLastError();
             c->adj_scratch = nullptr;
-            const size_t had = tape;
-            while (!tangent && budget > 0 && tape == had) plan(budget /= 2);
-            if (tape == had) return fail(c, BTO_ENOMEM, "adjoint scratch of %zu bytes", fixed + tape);
+            const size_t had = carry + tape;
+            while (carry + tape == had) {
+                if (!tangent && budget > 0) budget /= 2;
+                else if (carry && carry_words > 1) carry_words = 1;
+                else return fail(c, BTO_ENOMEM, "adjoint scratch of %zu bytes", fixed + carry + tape);
+                plan(budget);
+            }
         }
-        c->adj_bytes = fixed + tape;
+        c->adj_bytes = fixed + carry + tape;
     }
     char* base = static_cast<char*>(c->adj_scratch);
     std::vector<uint64_t> host(words);
@@ -1091,21 +1098,22 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
     }
     a.cot = d_cot_end;
     a.grad_seed = d_grad_seed;
-    uint32_t* nrec = reinterpret_cast<uint32_t*>(base + tab);
-    a.status = reinterpret_cast<uint8_t*>(base + tab + p4);
+    a.status = reinterpret_cast<uint8_t*>(base + tab);
     a.bad = a.status + p1;
     a.ckpt = use_ck ? c->ck_rec : reinterpret_cast<double*>(a.status + 3 * p1);
     a.ck_stride = use_ck ? c->cap * 3 : (int64_t)P * 3;
     a.rec_meta = use_ck ? c->rec_meta : nullptr;
-    a.tape = reinterpret_cast<TapeEntry*>(base + fixed);
+    a.carry = carry ? reinterpret_cast<uint32_t*>(base + fixed) : nullptr;
+    a.carry_acc = carry_words == ACC_WORDS;
+    a.tape = reinterpret_cast<TapeEntry*>(base + fixed + carry);
     a.status_out = d_status;
     a.f_base = f_base;
     a.call_first = sg_first;
+    a.call_last = sg_last;
     // carried from one launch to the next: by the caller of a segment, or, between
     // the groups of a call, in the gradients it returns
     a.lam = lam ? lam : d_grad_seed;
     a.drop = drop ? drop : a.bad + p1;
-    if (np < P || segs < nsg) a.nrec = nrec;
     const int md = mode | wide_grids(c, dtype);
     if (tangent) {
         a.np = (int64_t)P;

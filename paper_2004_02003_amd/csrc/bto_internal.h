@@ -160,6 +160,9 @@ struct TapeEntry {
     float f[3];
 };
 
+// Words per seed of what a launch leaves to the call's next: see AdjointArgs::carry.
+constexpr int ACC_WORDS = 27;
+
 struct AdjointArgs {
     const char* const* f;       // device array: grids of the call's cycles
     const double* h;            // device array: its step sizes
@@ -182,7 +185,11 @@ struct AdjointArgs {
     uint8_t* status_out;        // P (may be null): reported status
     const int32_t* rec_meta;    // non-null: take the forward from recorded checkpoints and these records
     GradRec grec;               // grid-gradient records (grec.key null: atomics)
-    uint32_t* nrec;             // P: records written by each seed so far in this call (null: one launch does all)
+    // Grid gradients between the launches of a call (null: one launch does all):
+    // P words, the records that each seed has written so far; with carry_acc 26 P
+    // more, its accumulator, which otherwise is flushed by each launch.
+    uint32_t* carry;
+    int32_t carry_acc;
     // Segments of this launch, sg_first down to sg_last (the whole interval:
     // nseg - 1 .. 0).  f, h and grad_f hold the grids, steps and gradient grids
     // from step f_base on.  lam (P x ncot x 3, cell units) carries the
@@ -191,7 +198,7 @@ struct AdjointArgs {
     // one launch does all) marks seeds dropped by an earlier launch.
     int32_t sg_first, sg_last;
     int32_t f_base;
-    int32_t call_first;         // first segment of this call
+    int32_t call_first, call_last;  // first and last segment of this call
     float* lam;
     uint8_t* drop;
 };
