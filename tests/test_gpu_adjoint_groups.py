@@ -122,3 +122,31 @@ def test_grid_gradients_do_not_depend_on_the_groups(dtype):
         b, sb, gb = _sweep(n, grids, times, seeds, cot, k, False, True)
         assert torch.equal(sa, sb) and torch.equal(a, b), k
         assert all(torch.equal(x, y) for x, y in zip(ga, gb)), k
+
+
+@pytest.mark.parametrize("k", [10, 25])
+def test_recorded_groups_sum_to_their_seed_subsets(k):
+    """Grid gradients from recorded checkpoints over several groups against
+    three subsets of the seeds that each fit one sweep: the same terms, up to
+    2,000 of one sign per point, added in another order.  Seed gradients are
+    the subsets' bits, also with three cotangents."""
+    P, N = 360_000, 50
+    n, grids, times, seeds, g = _block(P, N, torch.float16, 4)
+    cot = 0.5 + torch.rand((P, 1, 3), device="cuda", generator=g)
+    cot3 = torch.randn((P, 3, 3), device="cuda", generator=g)
+    _say(f"recorded groups, checkpoints every {k}")
+    a, sa, ga = _sweep(n, grids, times, seeds, cot, k, True, True)
+    j, sj, _ = _sweep(n, grids, times, seeds, cot3, k, True, False)
+    assert torch.equal(sa, sj) and int((sa == 0).sum()) > P // 2
+    total = [torch.zeros(v.shape, dtype=torch.float64, device="cuda") for v in grids]
+    for lo, hi in ((0, 100_000), (100_000, 230_000), (230_000, P)):
+        s, ss, gs = _sweep(n, grids, times, seeds[lo:hi].contiguous(), cot[lo:hi].contiguous(), k, True, True)
+        assert torch.equal(ss, sa[lo:hi]) and torch.equal(s, a[lo:hi]), (lo, hi)
+        for t, v in zip(total, gs):
+            t += v
+        s, ss, _ = _sweep(n, grids, times, seeds[lo:hi].contiguous(), cot3[lo:hi].contiguous(), k, True, False)
+        assert torch.equal(ss, sj[lo:hi]) and torch.equal(s, j[lo:hi]), (lo, hi)
+    top = max(float(t.abs().max()) for t in total)
+    assert top > 0
+    for t, v in zip(total, ga):
+        assert float((t - v).abs().max()) <= 2000 * 2.0 ** -24 * top
