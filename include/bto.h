@@ -288,7 +288,8 @@ int bto_get_tuning(const bto_ctx *ctx, bto_tuning *t);
  * the recorded flags.
  * Seeds that do not stay inside the block for the whole interval contribute
  * nothing: their gradient rows are zero.  Scratch of up to 1 GiB for the
- * stages (less where that much memory is not free), about
+ * stages (less where that much memory is not free: the context then keeps to
+ * what it got until a call needs more), about
  * n_seeds * n_steps / ckpt_every * 24 bytes for the positions and, for grid
  * gradients in several groups, 108 bytes per seed for the sums carried from one
  * to the next (a card without room for these sums gets them flushed by each

@@ -21,6 +21,10 @@ using namespace bto;
 // the three slots of live counts, ahead of the particle-step counters
 static constexpr size_t COUNT_BYTES = 3 * NSEG * CSTRIDE * sizeof(uint32_t);
 
+// Budget of the adjoint's tape: 64 bytes per step and seed, so 16.7 million
+// steps -- 330,000 seeds over 50 steps in one sweep.
+static constexpr size_t ADJ_TAPE_BYTES = (size_t)1 << 30;
+
 struct bto_ctx {
     bto_block blk;
     Geom geom;
@@ -61,6 +65,8 @@ struct bto_ctx {
     // adjoint scratch (grown on demand)
     void* adj_scratch = nullptr;
     size_t adj_bytes = 0;
+    size_t adj_budget = ADJ_TAPE_BYTES;    // tape and carried words per seed that the scratch was got for
+    size_t adj_carry_words = ACC_WORDS;
     // checkpoints recorded by BTO_RECORD_CKPT advection: ck_slots slots of cap x 3 doubles
     int ckpt_every = 10;          // tuning: spacing of recorded checkpoints
     double* ck_rec = nullptr;
@@ -998,10 +1004,6 @@ int bto_stats(bto_ctx* c, bto_stats_t* out, void* stream) {
 
 }  // extern "C"
 
-// Budget of the adjoint's tape: 64 bytes per step and seed, so 16.7 million
-// steps -- 330,000 seeds over 50 steps in one sweep.
-static constexpr size_t ADJ_TAPE_BYTES = (size_t)1 << 30;
-
 // The adjoint over checkpoint segments sg_first .. sg_last with the grids,
 // steps and gradient grids of steps f_base .. f_base + n_local (arguments
 // validated by the callers).  The tape comes from the adjoint's own forward
@@ -1028,7 +1030,7 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
     // single segment beyond it is swept for a part of the seeds at a time.  With
     // several groups, the gradient sums go from one to the next in memory.
     const size_t per = (size_t)K * 4 * sizeof(TapeEntry);
-    size_t np = 0, segs = 0, tape = 0, carry = 0, carry_words = ACC_WORDS;
+    size_t np = 0, segs = 0, tape = 0, carry = 0, carry_words = c->adj_carry_words;
     const auto plan = [&](size_t budget) {
         np = P;
         segs = budget / (P * per);
@@ -1045,7 +1047,8 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
         carry = d_grad_fields && segs < nsg ? (P * carry_words * sizeof(uint32_t) + 255) & ~(size_t)255 : 0;
     };
     hipError_t e;
-    size_t budget = ADJ_TAPE_BYTES;
+    // as long as the scratch holds what the last one got, there is nothing to ask for
+    size_t budget = c->adj_budget;
     if (!tangent) plan(budget);
     if (fixed + carry + tape > c->adj_bytes) {
         if (c->adj_scratch) {
@@ -1055,6 +1058,9 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
             c->adj_scratch = nullptr;
             c->adj_bytes = 0;
         }
+        budget = ADJ_TAPE_BYTES;
+        carry_words = ACC_WORDS;
+        if (!tangent) plan(budget);
         // a card without that much memory left gets by with a shorter tape, and in
         // the end with sums that each group flushes
         while (hipMalloc(&c->adj_scratch, fixed + carry + tape) != hipSuccess) {
@@ -1069,6 +1075,8 @@ static int adjoint_run(bto_ctx* c, const void* const* d_fields, const double* ti
             }
         }
         c->adj_bytes = fixed + carry + tape;
+        c->adj_budget = budget;
+        c->adj_carry_words = carry_words;
     }
     char* base = static_cast<char*>(c->adj_scratch);
     std::vector<uint64_t> host(words);

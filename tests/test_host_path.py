@@ -1,0 +1,133 @@
+"""The library's host code on a card that is short of memory, seen from outside:
+the library is loaded behind a HIP runtime without a device (fake_hip.c), which
+logs allocations, copies, waits and launches and refuses what it is told to.
+Each case runs in a process of its own.  No GPU."""
+
+import ctypes
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+ROCM = os.environ.get("ROCM_PATH", "/opt/rocm")
+STREAM = 7
+
+
+class Host:
+    """The library behind the fake runtime."""
+
+    def __init__(self, fake):
+        self.f = ctypes.CDLL(fake, mode=ctypes.RTLD_GLOBAL)
+        self.f.fake_log.restype = ctypes.c_char_p
+        self.f.fake_memory.argtypes = [ctypes.c_size_t]
+        sys.path.insert(0, os.path.join(ROOT, "paper_2004_02003_amd"))
+        import _lib
+
+        self.lib, self.L = _lib, _lib.load()
+
+    def create(self, n, cap):
+        b = self.lib.Block()
+        b.n[:], b.spacing[:] = n, [1.0] * 3
+        h = ctypes.c_void_p()
+        assert self.L.bto_create(ctypes.byref(b), cap, 0, ctypes.byref(h)) == 0
+        return h
+
+    def seed(self, h, P):
+        assert self.L.bto_seed_explicit(h, 1 << 50, P, STREAM) == 0
+
+    def tune(self, h, **kw):
+        t = self.lib.Tuning()
+        assert self.L.bto_get_tuning(h, ctypes.byref(t)) == 0
+        for k, v in kw.items():
+            setattr(t, k, v)
+        assert self.L.bto_set_tuning(h, ctypes.byref(t)) == 0
+
+    @staticmethod
+    def grids(N, at=1 << 51):
+        return (ctypes.c_void_p * (N + 1))(*[at + (q << 32) for q in range(N + 1)])
+
+    @staticmethod
+    def times(N):
+        return (ctypes.c_double * (N + 1))(*range(N + 1))
+
+    def logged(self, call):
+        """(status, log lines) of a call."""
+        self.f.fake_clear()
+        rc = call()
+        return rc, self.f.fake_log().decode().splitlines()
+
+    def advect(self, h, N, dtype=0, flags=0):
+        return self.logged(lambda: self.L.bto_advect_interval(h, self.grids(N), self.times(N), N, dtype, flags, STREAM))
+
+    def adjoint(self, h, N, k, grads=False):
+        return self.logged(lambda: self.L.bto_adjoint_interval(
+            h, self.grids(N), self.times(N), N, 0, 0, 1 << 50, 1, 1 << 50,
+            self.grids(N, 1 << 52) if grads else None, None, k, STREAM))
+
+
+def launches(log):
+    return [ln for ln in log if ln.startswith("launch")]
+
+
+def memory_calls(log):
+    return [ln for ln in log if re.match("malloc|free|sync|memset|copy", ln)]
+
+
+def case_adjoint_keeps_the_tape_it_got(grads):
+    """The first call settles for a shorter tape; the next ones use it without
+    asking again."""
+    host = Host(sys.argv[1])
+    h = host.create((27, 22, 17), 400_000)
+    host.seed(h, 400_000)
+    if grads:  # the records are in place; the scratch of one position per seed has to grow
+        assert host.adjoint(h, 50, 50, True)[0] == 0
+    host.f.fake_memory(0 if grads else 640 << 20)
+    rc, first = host.adjoint(h, 50, 10, grads)
+    assert rc == 0, rc
+    tried = [ln for ln in first if ln.startswith("malloc")]
+    assert any("failed" in ln for ln in tried) and "ok" in tried[-1], first
+    for _ in range(2):
+        rc, again = host.adjoint(h, 50, 10, grads)
+        assert rc == 0
+        assert not memory_calls(again), again
+        assert launches(again) == launches(first)
+
+
+def case_adjoint_recovers(_):
+    host = Host(sys.argv[1])
+    h = host.create((27, 22, 17), 400_000)
+    host.seed(h, 360_000)
+    host.f.fake_memory(1 << 20)
+    assert host.adjoint(h, 50, 10)[0] == host.lib.BTO_ENOMEM
+    host.f.fake_memory(4 << 30)
+    rc, log = host.adjoint(h, 50, 10)
+    assert rc == 0 and [ln for ln in log if ln.startswith("malloc")] == [log[0]] and "ok" in log[0], log
+    assert host.L.bto_destroy(h) == 0 and host.f.fake_blocks() == 0
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    from paper_2004_02003_amd import _lib
+
+    if not os.path.exists(_lib.LIB_PATH):
+        pytest.skip("libbto.so not built")
+    out = str(tmp_path_factory.mktemp("fake") / "fake_hip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-I", os.path.join(ROCM, "include"),
+                    os.path.join(HERE, "fake_hip.c"), "-o", out], check=True)
+    return out
+
+
+@pytest.mark.parametrize("case,arg", [("adjoint_keeps_the_tape_it_got", 0), ("adjoint_keeps_the_tape_it_got", 1),
+                                      ("adjoint_recovers", 0)])
+def test_host(fake, case, arg):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), fake, case, str(arg)], capture_output=True,
+                       text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+if __name__ == "__main__":
+    globals()["case_" + sys.argv[2]](int(sys.argv[3]))
