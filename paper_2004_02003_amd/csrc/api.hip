@@ -574,14 +574,23 @@ static int rebin(bto_ctx* c, hipStream_t s) {
         const size_t tb = rebin_temp_bytes((int64_t)NSEG * nbins);
         if (tb == 0) return fail(c, BTO_EHIP, "rebin: scan storage query failed");
         const size_t words = (size_t)c->cap * 2 + (size_t)NSEG * nbins * 2;
-        if (hipMalloc(&c->rebin_buf, words * sizeof(uint32_t)) != hipSuccess ||
-            hipMalloc(&c->rebin_temp, tb) != hipSuccess) {
+        uint32_t* buf = nullptr;
+        void* temp = nullptr;
+        if (hipMalloc(&buf, words * sizeof(uint32_t)) != hipSuccess || hipMalloc(&temp, tb) != hipSuccess) {
             (void)hipGetLastError();
+            if (buf) (void)hipFree(buf);
             return fail(c, BTO_ENOMEM, "rebin buffers");
         }
-        // the bin counts start at zero once; each rebin leaves them zero again
-        if (hipMemset(c->rebin_buf + (size_t)c->cap * 2, 0, (size_t)NSEG * nbins * sizeof(uint32_t)) != hipSuccess)
-            return fail(c, BTO_EHIP, "rebin: clearing bin counts failed");
+        // the bin counts start at zero once, on the stream that counts first; each
+        // rebin leaves them zero again
+        const hipError_t e = launch_tile_fill(buf + (size_t)c->cap * 2, (size_t)NSEG * nbins, s);
+        if (e != hipSuccess) {
+            (void)hipFree(buf);
+            (void)hipFree(temp);
+            return hip_fail(c, e, "rebin: clearing bin counts");
+        }
+        c->rebin_buf = buf;
+        c->rebin_temp = temp;
         c->rebin_temp_bytes = tb;
     }
     RebinArgs a{};

@@ -109,6 +109,30 @@ def case_adjoint_recovers(_):
     assert host.L.bto_destroy(h) == 0 and host.f.fake_blocks() == 0
 
 
+def case_rebin_buffers(_):
+    """A re-sort whose second buffer cannot be had leaves nothing behind; the
+    next one gets both and clears the bin counts on the caller's stream, ahead
+    of the kernel that counts into them (the null stream would not be ordered
+    with a stream created non-blocking)."""
+    host = Host(sys.argv[1])
+    h = host.create((64, 64, 64), 40_000)
+    host.tune(h, rebin_every=1)
+    host.seed(h, 40_000)
+    held = host.f.fake_blocks()
+    host.f.fake_fail(1)
+    rc, log = host.advect(h, 4)
+    assert rc == host.lib.BTO_ENOMEM and host.f.fake_blocks() == held, (rc, log)
+    rc, log = host.advect(h, 4)
+    assert rc == 0 and len([ln for ln in log if ln.startswith("malloc") and "ok" in ln]) == 2, log
+    assert not [ln for ln in log if ln.startswith("memset")], log
+    kernels = launches(log)
+    assert all(ln.endswith("stream 0x7") for ln in kernels), log
+    fill = next(i for i, ln in enumerate(kernels) if "tile_fill_kernel" in ln)
+    assert fill < next(i for i, ln in enumerate(kernels) if "rebin_count_kernel" in ln)
+    assert len([ln for ln in kernels if "tile_fill_kernel" in ln]) == 1
+    assert host.L.bto_destroy(h) == 0 and host.f.fake_blocks() == 0
+
+
 @pytest.fixture(scope="module")
 def fake(tmp_path_factory):
     from paper_2004_02003_amd import _lib
@@ -122,7 +146,7 @@ def fake(tmp_path_factory):
 
 
 @pytest.mark.parametrize("case,arg", [("adjoint_keeps_the_tape_it_got", 0), ("adjoint_keeps_the_tape_it_got", 1),
-                                      ("adjoint_recovers", 0)])
+                                      ("adjoint_recovers", 0), ("rebin_buffers", 0)])
 def test_host(fake, case, arg):
     r = subprocess.run([sys.executable, os.path.abspath(__file__), fake, case, str(arg)], capture_output=True,
                        text=True, timeout=120)
