@@ -141,12 +141,13 @@ static void set_segments(bto_ctx* c, int64_t P) {
 }
 
 // Workgroups per segment, one batch of particles each; per_cu > 0: at most that
-// many per CU, which then loop over the batches.
+// many per CU, which then loop over the batches, as they do where the launch
+// would have 2^32 threads or more (two lanes each for over 2^31 particles).
 static int blocks_per_seg(const bto_ctx* c, int64_t max_seg, int per_cu) {
-    int64_t need = (max_seg + BLOCK - 1) / BLOCK;
-    const int64_t lim = (int64_t)c->cus_per_xcd * per_cu;
+    int64_t need = (max_seg + BLOCK - 1) / BLOCK, lim = 0xFFFFFFFFll / (BLOCK * NSEG);
+    if (per_cu > 0) lim = (int64_t)c->cus_per_xcd * per_cu;
     if (need < 1) need = 1;
-    return (int)(per_cu > 0 && lim < need ? lim : need);
+    return (int)(need < lim ? need : lim);
 }
 
 extern "C" {

@@ -92,8 +92,14 @@ hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
 hipError_t hipSetDevice(int d) { return d == 0 ? hipSuccess : hipErrorInvalidDevice; }
 hipError_t hipGetDevice(int *d) { return *d = 0, hipSuccess; }
 hipError_t hipGetDeviceCount(int *n) { return *n = 1, hipSuccess; }
-hipError_t hipGetLastError(void) { return hipSuccess; }
-hipError_t hipPeekAtLastError(void) { return hipSuccess; }
+static hipError_t last = hipSuccess;
+hipError_t hipPeekAtLastError(void) { return last; }
+hipError_t hipGetLastError(void) {
+    const hipError_t e = last;
+    last = hipSuccess;
+    return e;
+}
+
 const char *hipGetErrorString(hipError_t e) { return e == hipSuccess ? "success" : "error"; }
 hipError_t hipFuncSetAttribute(const void *f, hipFuncAttribute a, int v) { return (void)f, (void)a, (void)v, hipSuccess; }
 hipError_t hipGetSymbolAddress(void **p, const void *s) { return *p = (void *)s, hipSuccess; }
@@ -159,5 +165,6 @@ hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, si
     for (int i = 0; i < n_kernels; ++i)
         if (kernels[i].host == f) name = kernels[i].name;
     say("launch %s grid %u %u block %u stream %p", name, grid.x, grid.y, block.x, (void *)stream);
-    return (uint64_t)grid.x * block.x > 0xFFFFFFFFull ? hipErrorInvalidConfiguration : hipSuccess;
+    if ((uint64_t)grid.x * block.x <= 0xFFFFFFFFull) return hipSuccess;
+    return last = hipErrorInvalidConfiguration; /* a grid's threads per axis fit 32 bits */
 }

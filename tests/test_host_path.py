@@ -133,6 +133,20 @@ def case_rebin_buffers(_):
     assert host.L.bto_destroy(h) == 0 and host.f.fake_blocks() == 0
 
 
+def case_launches_of_many_particles(lanes):
+    """2.15 thousand million particles, 215 GB of state: with two lanes each a
+    launch of one batch per workgroup would pass 2^32 threads."""
+    host = Host(sys.argv[1])
+    P = 2_150_000_000
+    h = host.create((64, 64, 64), P)
+    host.tune(h, lanes_per_particle=lanes)
+    host.seed(h, P)
+    rc, log = host.advect(h, 2)
+    assert rc == 0, (rc, log)
+    blocks, threads = map(int, re.search(r"advect_kernel.* grid (\d+) 1 block (\d+)", log[-1]).groups())
+    assert 2 ** 31 < blocks * threads < 2 ** 32
+
+
 @pytest.fixture(scope="module")
 def fake(tmp_path_factory):
     from paper_2004_02003_amd import _lib
@@ -146,7 +160,8 @@ def fake(tmp_path_factory):
 
 
 @pytest.mark.parametrize("case,arg", [("adjoint_keeps_the_tape_it_got", 0), ("adjoint_keeps_the_tape_it_got", 1),
-                                      ("adjoint_recovers", 0), ("rebin_buffers", 0)])
+                                      ("adjoint_recovers", 0), ("rebin_buffers", 0), ("launches_of_many_particles", 1),
+                                      ("launches_of_many_particles", 2)])
 def test_host(fake, case, arg):
     r = subprocess.run([sys.executable, os.path.abspath(__file__), fake, case, str(arg)], capture_output=True,
                        text=True, timeout=120)
