@@ -784,22 +784,37 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
     // FP32 particles far apart (less than one per four cells) share few lines, and
     // those of four or five workgroups do not stay in a CU's L1 from one step of
     // a launch to the next: two at a time do (LDS they do not use keeps the
-    // others out).  The f32 block above: launches of 2 steps 4.00 ms instead of
-    // 4.13, of 5 steps 3.63 instead of 3.93 (re-sorted after each: 3.99 instead of
-    // 4.20 for 25 steps), of 20 steps 3.60 instead of 4.27; one step 5.00 instead
-    // of 5.03.  Where the chip holds every workgroup at once anyway, two rounds of
-    // two pay off later (128^3 ABC, 4 per CU: 5 steps 0.47 instead of 0.46, 25
-    // steps 0.676 instead of 0.700).  It does not pay with a particle in every
-    // cell (200 x 180 x 150, 5 steps: 2.34 instead of 2.07, bf16); for 16-bit
-    // grids, whose lines hold twice the cells (200^3 ABC, f16: 0.93 instead of
-    // 0.69); for one level per step (200 x 190 x 180 ABC, frozen: 0.86 instead of
-    // 0.83); with FP64 sampling, whose chains are longer (180^3 ABC: 1.00 instead
-    // of 0.94); nor for two lanes per particle (the f32 block re-sorted every 5
-    // steps: 3.88 instead of 3.68).
+    // others out).  What they gain grows with the steps of a launch and, as the
+    // chip has more rounds of them to hide a launch's two ends in, with the
+    // workgroups per CU; a flow slow enough to stay in its lines loses both.  24
+    // steps, two at a time against all (us):
+    //                       launches of   2           5           8           24
+    //   turbulence   174^3 (10 per CU)  1470 1530   1386 1444   1362 1450   1477 1635
+    //                256^3 (32)         4911 5105   4482 4870   4532 5100   4595 5455
+    //   ABC          146^3 (5.9)         442  385    332  303    306  284    276  263
+    //                174^3               672  566    532  482    476  448    418  404
+    //                256^3              2020 1792   1525 1414   1377 1302   1197 1150
+    // The looping grids of four per CU took 604, 506, 471 and 428 for the ABC flow
+    // at 174^3 and 1977, 1557, 1421 and 1247 at 256^3: from about 180 steps times
+    // workgroups per CU on no launch is slower than those.  Up to four per CU run
+    // at once, and in two full rounds if they are nearly four (128^3 ABC: 164
+    // instead of 166 in one launch, 176 and 175 in two, 187 and 182 in three; but
+    // 222 instead of 189 at 112^3, 2.7 per CU, and 308 instead of 291 at 132^3,
+    // 4.4).  A caller that re-sorts has a flow that mixes, and launches of a few
+    // steps (256^3 turbulence re-sorted every 2, 5 and 10: 4324, 3835, 4115 instead
+    // of 4495, 4036, 4545; 146^3: 948, 774, 787 instead of 980, 811, 818).
+    // It does not pay with a particle in every cell (200 x 180 x 150, bf16,
+    // launches of 5: 2.91 ms instead of 2.71); for 16-bit grids, whose lines hold
+    // twice the cells (200^3 ABC, f16: 0.93 instead of 0.72); for one level per
+    // step (200 x 190 x 180 ABC, frozen: 0.87 instead of 0.81); with FP64 sampling,
+    // whose chains are longer (180^3 ABC: 1.02 instead of 0.91); nor for two lanes
+    // per particle (256^3 turbulence re-sorted every 5 steps: 3.90 instead of 3.69).
     const int64_t cells = (int64_t)(c->blk.n[0] - 1) * (c->blk.n[1] - 1) * (c->blk.n[2] - 1);
+    const int cu = c->cus_per_xcd;
+    const bool rounds = R >= 5 * cu || (5 * R > 18 * cu && R <= 4 * cu);
     const bool may_pair = dtype == BTO_F32 && (mode & ~MODE_WIDE) == MODE_LINEAR && lpp == 1 && per_cu == 0 &&
-                          4 * c->n_seeds <= cells;
-    const int pair_from = R >= 6 * c->cus_per_xcd ? 2 : 8;
+                          4 * c->n_seeds <= cells && rounds;
+    const int pair_from = c->rebin_every > 0 ? (R >= 6 * cu ? 2 : 12) : (R >= 5 * cu ? (180 * cu + R - 1) / R : 12);
     // launches of (nearly) equal length, at most steps_per_launch steps each
     int kmax = c->steps_per_launch;
     if (c->rebin_every > 0 && c->rebin_every < kmax) kmax = c->rebin_every;

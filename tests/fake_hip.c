@@ -161,10 +161,10 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, hipSt
 
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, hipStream_t stream) {
     const char *name = "?";
-    (void)args, (void)lds;
+    (void)args;
     for (int i = 0; i < n_kernels; ++i)
         if (kernels[i].host == f) name = kernels[i].name;
-    say("launch %s grid %u %u block %u stream %p", name, grid.x, grid.y, block.x, (void *)stream);
+    say("launch %s grid %u %u block %u lds %zu stream %p", name, grid.x, grid.y, block.x, lds, (void *)stream);
     if ((uint64_t)grid.x * block.x <= 0xFFFFFFFFull) return hipSuccess;
     return last = hipErrorInvalidConfiguration; /* a grid's threads per axis fit 32 bits */
 }

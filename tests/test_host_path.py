@@ -147,6 +147,25 @@ def case_launches_of_many_particles(lanes):
     assert 2 ** 31 < blocks * threads < 2 ** 32
 
 
+def case_pairs_of_workgroups(_):
+    """Which FP32 launches keep all but two workgroups off a CU (by LDS they do
+    not use): lattices of stride 2, launches of `steps`, re-sorted or not."""
+    host = Host(sys.argv[1])
+    for n, steps, rebin, pair in [
+            (112, 24, 0, False), (112, 24, 24, False), (128, 8, 0, False), (128, 12, 0, True), (132, 32, 0, False),
+            (146, 24, 0, False), (146, 31, 0, True), (146, 2, 2, False), (150, 2, 2, True), (150, 2, 0, False), (174, 8, 0, False),
+            (174, 24, 0, True), (256, 2, 0, False), (256, 5, 0, False), (256, 6, 0, True), (256, 2, 2, True),
+            (256, 1, 1, False)]:
+        h = host.create((n, n, n), (n // 2) ** 3)
+        host.tune(h, rebin_every=rebin, steps_per_launch=32)
+        host.seed(h, (n // 2) ** 3)
+        rc, log = host.advect(h, steps)
+        assert rc == 0
+        lds = [int(re.search(r" lds (\d+)", ln).group(1)) for ln in launches(log) if "advect_kernel" in ln]
+        assert len(lds) == 1 and (lds[0] > 0) == pair, (n, steps, rebin, log)
+        assert host.L.bto_destroy(h) == 0
+
+
 @pytest.fixture(scope="module")
 def fake(tmp_path_factory):
     from paper_2004_02003_amd import _lib
@@ -161,7 +180,7 @@ def fake(tmp_path_factory):
 
 @pytest.mark.parametrize("case,arg", [("adjoint_keeps_the_tape_it_got", 0), ("adjoint_keeps_the_tape_it_got", 1),
                                       ("adjoint_recovers", 0), ("rebin_buffers", 0), ("launches_of_many_particles", 1),
-                                      ("launches_of_many_particles", 2)])
+                                      ("launches_of_many_particles", 2), ("pairs_of_workgroups", 0)])
 def test_host(fake, case, arg):
     r = subprocess.run([sys.executable, os.path.abspath(__file__), fake, case, str(arg)], capture_output=True,
                        text=True, timeout=120)
