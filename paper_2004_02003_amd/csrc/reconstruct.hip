@@ -41,7 +41,8 @@ __global__ __launch_bounds__(BLOCK) void recon_init_kernel(int64_t P, double* en
 
 constexpr int MAX_LINE = 1024;  // a lattice line never exceeds the grid's points per axis
 
-// The x pass: one wavefront per line, read in chunks of 64 entries.  A ballot
+// The x pass, and the y and z passes of lattices with few lines (see below): one
+// wavefront per line, read in chunks of 64 entries.  A ballot
 // per chunk marks the known ones, and every unknown entry finds its nearest
 // known neighbours from the ballot masks (below: highest set bit under its
 // lane, carried across chunks left to right; above: lowest set bit over its
@@ -50,14 +51,18 @@ constexpr int MAX_LINE = 1024;  // a lattice line never exceeds the grid's point
 // states come from the flags and are all written, with NaN for the entries
 // that stay missing.
 // NC: chunks there is room for (2 for lines of up to 128 entries, 16 for all).
-template <bool INIT, int NC>
-__global__ __launch_bounds__(BLOCK) void recon_x_kernel(int64_t n_lines, int32_t len, double* end,
-                                                        const uint8_t* flag, uint8_t* state) {
+// X: lines along x, contiguous; otherwise point stride st, lines indexed by x
+// (n_a of them) and the other axis, whose stride is s_b.
+template <bool INIT, bool X, int NC>
+__global__ __launch_bounds__(BLOCK) void recon_line_kernel(int64_t n_lines, int32_t n_a, int64_t s_b, int32_t len,
+                                                           int64_t st, double* end, const uint8_t* flag,
+                                                           uint8_t* state) {
 #pragma clang fp contract(off)  // Eq. (1) rounded as written: two products, one sum
     const int64_t line = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) / WAVE;
     const int lane = threadIdx.x % WAVE;
     if (line >= n_lines) return;  // whole wavefronts leave together
-    const int64_t base = line * len;
+    const int64_t base = X ? line * len : line % n_a + line / n_a * s_b;
+    const auto at = [&](int i) { return base + (X ? (int64_t)i : (int64_t)i * st); };
     const int nchunk = (len + WAVE - 1) / WAVE;
     unsigned long long mask[NC];
 #pragma unroll
@@ -65,7 +70,7 @@ __global__ __launch_bounds__(BLOCK) void recon_x_kernel(int64_t n_lines, int32_t
         mask[c] = 0ull;
         if (c < nchunk) {
             const int i = c * WAVE + lane;
-            const bool known = i < len && (INIT ? flag[base + i] == (uint8_t)S_VALID : state[base + i] != ST_MISSING);
+            const bool known = i < len && (INIT ? flag[at(i)] == (uint8_t)S_VALID : state[at(i)] != ST_MISSING);
             mask[c] = __ballot(known);
         }
     }
@@ -99,19 +104,19 @@ __global__ __launch_bounds__(BLOCK) void recon_x_kernel(int64_t n_lines, int32_t
             // Eq. (1): L(x1) = (x1 - x0)/(x2 - x0) f(x2) + (x2 - x1)/(x2 - x0) f(x0)
             const double span = (double)(hi - lo[c]);
             const double w2 = (double)(i - lo[c]) / span, w0 = (double)(hi - i) / span;
-            const int64_t q0 = base + lo[c], q2 = base + hi, r = base + i;
+            const int64_t q0 = at(lo[c]), q2 = at(hi), r = at(i);
 #pragma unroll
             for (int d = 0; d < 3; ++d) end[3 * r + d] = w2 * end[3 * q2 + d] + w0 * end[3 * q0 + d];
         }
         if (INIT) {
-            state[base + i] = known ? ST_KNOWN : fill ? ST_REBUILT : ST_MISSING;
+            state[at(i)] = known ? ST_KNOWN : fill ? ST_REBUILT : ST_MISSING;
             if (!known && !fill) {
                 const double nan = __builtin_nan("");
 #pragma unroll
-                for (int d = 0; d < 3; ++d) end[3 * (base + i) + d] = nan;
+                for (int d = 0; d < 3; ++d) end[3 * at(i) + d] = nan;
             }
         } else if (fill) {
-            state[base + i] = ST_REBUILT;
+            state[at(i)] = ST_REBUILT;
         }
     }
 }
@@ -125,6 +130,12 @@ __global__ __launch_bounds__(BLOCK) void recon_x_kernel(int64_t n_lines, int32_t
 // for its pieces, the nearest known entries outside them from the other
 // masks, and fills.
 constexpr int PIECE = 8, YZ_BLOCK = 16 * WAVE;
+// Fewer lines leave three quarters of the CUs without a workgroup of 64, and each
+// wavefront with pieces to fill one after the other.  A rebuild with random
+// missing entries (30% / 90%), all passes by a wavefront per line against this:
+// 4 x 1000 x 4 28 / 29 us and 60 / 61, 3 x 300 x 300 37 / 35 and 62 / 76,
+// 16 x 128 x 128 21 / 22 and 27 / 32, 64^3 15 / 15 and 15 / 19.
+constexpr int64_t FEW_LINES = 4096;
 
 __global__ __launch_bounds__(YZ_BLOCK) void recon_yz_kernel(int64_t n_lines, int32_t n_a, int64_t s_b, int32_t len,
                                                             int64_t st, double* end, uint8_t* state) {
@@ -289,24 +300,33 @@ hipError_t launch_reconstruct(const int32_t m[3], double* end, const uint8_t* fl
     // many lanes idle to make the states on the way.
     const int64_t xl = (int64_t)m[1] * m[2], xb = (xl * WAVE + BLOCK - 1) / BLOCK;  // one wavefront per line
     if (m[0] >= WAVE / 2) {
-        const auto kernel = m[0] <= 2 * WAVE ? recon_x_kernel<true, 2> : recon_x_kernel<true, MAX_LINE / WAVE>;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)xb), dim3(BLOCK), 0, s, xl, m[0], end, flag, state);
+        const auto kernel = m[0] <= 2 * WAVE ? recon_line_kernel<true, true, 2>
+                                             : recon_line_kernel<true, true, MAX_LINE / WAVE>;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)xb), dim3(BLOCK), 0, s, xl, 1, 0, m[0], 1, end, flag, state);
     } else {
         hipLaunchKernelGGL(recon_init_kernel, dim3(grid_for(P)), dim3(BLOCK), 0, s, P, end, flag, state);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         if (m[0] >= 3)
-            hipLaunchKernelGGL((recon_x_kernel<false, 2>), dim3((unsigned)xb), dim3(BLOCK), 0, s, xl, m[0], end, flag,
-                               state);
+            hipLaunchKernelGGL((recon_line_kernel<false, true, 2>), dim3((unsigned)xb), dim3(BLOCK), 0, s, xl, 1, 0, m[0],
+                               1, end, flag, state);
     }
     hipError_t e = hipGetLastError();
     // y pass: lines over (x, z); z pass: lines over (x, y)
     const int64_t sy = m[0], sz = (int64_t)m[0] * m[1];
     for (int axis = 1; axis < 3 && e == hipSuccess; ++axis) {
         const int64_t lines = axis == 1 ? (int64_t)m[0] * m[2] : (int64_t)m[0] * m[1];
+        const int64_t s_b = axis == 1 ? sz : sy, st = axis == 1 ? sy : sz;
         if (m[axis] < 3) continue;
-        hipLaunchKernelGGL(recon_yz_kernel, dim3((unsigned)((lines + WAVE - 1) / WAVE)), dim3(YZ_BLOCK), 0, s, lines,
-                           m[0], axis == 1 ? sz : sy, m[axis], axis == 1 ? sy : sz, end, state);
+        if (lines < FEW_LINES) {
+            const auto kernel = m[axis] <= 2 * WAVE ? recon_line_kernel<false, false, 2>
+                                                    : recon_line_kernel<false, false, MAX_LINE / WAVE>;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((lines * WAVE + BLOCK - 1) / BLOCK)), dim3(BLOCK), 0, s, lines,
+                               m[0], s_b, m[axis], st, end, flag, state);
+        } else {
+            hipLaunchKernelGGL(recon_yz_kernel, dim3((unsigned)((lines + WAVE - 1) / WAVE)), dim3(YZ_BLOCK), 0, s, lines,
+                               m[0], s_b, m[axis], st, end, state);
+        }
         e = hipGetLastError();
     }
     return e;
