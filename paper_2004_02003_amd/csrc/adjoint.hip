@@ -36,8 +36,9 @@
 // the second.  One sweep that recomputed and reversed one segment after the
 // other, each step in dependent loads, took 541 and 935 us in all.
 //
-// The Jacobian of a recomputed interval needs no reverse sweep at all: see
-// adj_tangent_kernel.
+// The Jacobian of a recomputed interval, and the seed gradients of many seeds
+// over a few steps at a time, need no reverse sweep at all: see
+// adj_tangent_kernel and adj_segments_kernel.
 #include "bto_internal.h"
 
 namespace bto {
@@ -220,8 +221,9 @@ struct TapeHook {
 
 // The tangent T = d x_n / d x_0 (cell units) carried along the steps: dk_s =
 // G_s dy_s with the stage points' derivatives dy_s, as the step combines the
-// stage velocities.
-template <int MODE>
+// stage velocities.  DEV: T and the stage points' derivatives without their unit
+// matrix, whose ones would round what a few steps add to them.
+template <int MODE, bool DEV = false>
 struct TangentHook {
     const Geom& g;
     float T[3][3], Y[3][3], S[3][3], h;
@@ -245,8 +247,11 @@ struct TangentHook {
 #pragma unroll
         for (int r = 0; r < 3; ++r)
 #pragma unroll
-            for (int k = 0; k < 3; ++k)
-                K[r][k] = (float)g.inv_sp[r] * (D[r][0] * Y[0][k] + D[r][1] * Y[1][k] + D[r][2] * Y[2][k]);
+            for (int k = 0; k < 3; ++k) {
+                float v = D[r][0] * Y[0][k] + D[r][1] * Y[1][k] + D[r][2] * Y[2][k];
+                if constexpr (DEV) v += D[r][k];
+                K[r][k] = (float)g.inv_sp[r] * v;
+            }
 #pragma unroll
         for (int r = 0; r < 3; ++r)
 #pragma unroll
@@ -311,6 +316,69 @@ __device__ __forceinline__ int forward_status(const AdjointArgs& a, int64_t p) {
     if (!a.rec_meta) return (int)a.status[p];
     const int32_t meta = a.rec_meta[p];
     return meta == META_LIVE ? S_VALID : (int)((uint32_t)meta >> META_SHIFT);
+}
+
+// Few steps at a time, no grid gradients, many seeds (see SHORT_SEEDS): segment
+// by segment from the last one of the call, the tangent along the segment's
+// steps from its recorded checkpoint and the cotangents through its transpose; a
+// recomputed step that does not stay inside drops the seed, as in
+// adj_recompute_kernel.  Without a record (rec_meta null): one segment, the whole
+// interval from the seeds, whose status is the one found here.
+template <int DT, int MODE>
+__global__ __launch_bounds__(ADJ_BLOCK) void adj_segments_kernel(const AdjointArgs a) {
+    const int64_t p = (int64_t)blockIdx.x * ADJ_BLOCK + threadIdx.x;
+    if (p >= a.P) return;
+    const int nseg = (a.N + a.k - 1) / a.k;
+    const bool own = !a.rec_meta, first = a.sg_first == nseg - 1, last = a.sg_last == 0;
+    int status = own ? S_VALID : forward_status(a, p);
+    const int prior = !first ? (int)a.drop[p] : 0;
+    const bool on = status == S_VALID && !prior;
+    float lam[3][3];
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const float* src = first ? a.cot : a.lam;
+            lam[m][d] = on && m < a.ncot ? src[(p * a.ncot + m) * 3 + d] * (first ? (float)a.sp[d] : 1.f) : 0.f;
+        }
+    bool left = false;
+    if (on) {
+        for (int sg = a.sg_first; sg >= a.sg_last; --sg) {
+            const int n0 = sg * a.k, n1 = n0 + a.k < a.N ? n0 + a.k : a.N;
+            double x[3];
+#pragma unroll
+            for (int d = 0; d < 3; ++d)
+                x[d] = own ? (a.seed_xyz[3 * p + d] - a.origin[d]) * a.g.inv_sp[d]
+                           : a.ckpt[a.ck_stride * (int64_t)sg + 3 * p + d];
+            TangentHook<MODE, true> hook{a.g, {}, {}, {}, 0.f};
+            int st = S_TERMINATED;
+            if (inside(a.g, x)) st = adj_steps<DT, MODE>(a, x, n0, n1, hook);
+            if (st != S_VALID) {
+                if (own) status = st;
+                left = true;
+                break;
+            }
+#pragma unroll
+            for (int m = 0; m < 3; ++m) {
+                float l[3];
+#pragma unroll
+                for (int d = 0; d < 3; ++d)
+                    l[d] = lam[m][d] + (hook.T[0][d] * lam[m][0] + hook.T[1][d] * lam[m][1] + hook.T[2][d] * lam[m][2]);
+#pragma unroll
+                for (int d = 0; d < 3; ++d) lam[m][d] = l[d];
+            }
+        }
+    }
+    const int drop = left && !own ? ADJ_DROPPED : prior;
+    if (first || drop != prior) a.drop[p] = (uint8_t)drop;
+    if (last && a.status_out) a.status_out[p] = (uint8_t)(drop ? drop : status);
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+#pragma unroll
+        for (int d = 0; d < 3; ++d)
+            if (m < a.ncot)
+                (last ? a.grad_seed : a.lam)[(p * a.ncot + m) * 3 + d] =
+                    left ? 0.f : lam[m][d] * (last ? (float)a.g.inv_sp[d] : 1.f);
 }
 
 // Workgroup row y: segment sg_last + y.  A recomputed step that does not stay
@@ -595,6 +663,14 @@ hipError_t launch_adj_forward(const AdjointArgs& a, int dtype, int mode, hipStre
 hipError_t launch_adj_tangent(const AdjointArgs& a, int dtype, int mode, hipStream_t s) {
     return adj_dispatch(dtype, mode, [&](auto dt, auto md) {
         hipLaunchKernelGGL((adj_tangent_kernel<decltype(dt)::value, decltype(md)::value>), dim3(adj_blocks(a)),
+                           dim3(ADJ_BLOCK), 0, s, a);
+        return hipGetLastError();
+    });
+}
+
+hipError_t launch_adj_segments(const AdjointArgs& a, int dtype, int mode, hipStream_t s) {
+    return adj_dispatch(dtype, mode, [&](auto dt, auto md) {
+        hipLaunchKernelGGL((adj_segments_kernel<decltype(dt)::value, decltype(md)::value>), dim3(adj_blocks(a)),
                            dim3(ADJ_BLOCK), 0, s, a);
         return hipGetLastError();
     });

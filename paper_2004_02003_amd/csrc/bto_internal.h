@@ -398,6 +398,7 @@ int advect_max_blocks_per_cu(int dtype, int mode, int lanes_per_particle, int re
 // over them.  mode: MODE_WIDE set for grids beyond 4 GiB.
 hipError_t launch_adj_forward(const AdjointArgs& a, int dtype, int mode, hipStream_t s);
 hipError_t launch_adj_tangent(const AdjointArgs& a, int dtype, int mode, hipStream_t s);  // see the kernel
+hipError_t launch_adj_segments(const AdjointArgs& a, int dtype, int mode, hipStream_t s);  // see the kernel
 hipError_t launch_adj_recompute(const AdjointArgs& a, int dtype, int mode, hipStream_t s);
 hipError_t launch_adj_reverse(const AdjointArgs& a, int dtype, int mode, hipStream_t s);
 // n 64-bit words from the host into device memory, as kernel arguments (no
