@@ -99,7 +99,6 @@ struct bto_ctx {
     uint32_t* bid[2] = {nullptr, nullptr};
     int tb = 0;                   // bucket buffer of the current step
     int tile_live_slot = 0;       // count slot that holds the live particles of the tile layout
-    int32_t tile_step0 = 0;       // steps done when the tile layout was entered
     std::string err;
 };
 
@@ -458,7 +457,6 @@ static int tile_enter(bto_ctx* c, int dtype, int max_seg_blocks, hipStream_t s) 
     if (e != hipSuccess) return hip_fail(c, e, "tile bin launch");
     c->tile_layout = true;
     c->tile_live_slot = c->slot;
-    c->tile_step0 = c->steps_done;
     return BTO_OK;
 }
 
@@ -524,7 +522,7 @@ static int tile_step(bto_ctx* c, const void* f0, const void* f1, double h, int d
     a.psteps = c->psteps;
     a.live = c->counts + NSEG * CSTRIDE * c->tile_live_slot;
     a.backwards = c->steps_done & 1;
-    a.attempts = (uint32_t)(c->steps_done - c->tile_step0 + 1);
+    a.attempts = (uint32_t)(c->steps_done + 1);
     int64_t lg = c->n_seeds / (BLOCK * 32);
     lg = lg < 64 ? 64 : (lg > 1024 ? 1024 : lg);
     hipError_t e;
@@ -1031,8 +1029,8 @@ int bto_stats(bto_ctx* c, bto_stats_t* out, void* stream) {
     for (int x = 0; x < NSEG; ++x) live += cnt[x * CSTRIDE];
     unsigned long long ps = 0;
     for (int x = 0; x < NSEG; ++x) ps += psv[x * PSTRIDE];
-    // the tile steps count the attempts of the particles that ended; the live ones attempted every step
-    if (c->tile_layout) ps += (unsigned long long)live * (unsigned long long)(c->steps_done - c->tile_step0);
+    // the kernels count the steps of the particles that ended; the live ones attempted every step
+    ps += (unsigned long long)live * (unsigned long long)c->steps_done;
     out->n_live = live;
     out->particle_steps = (int64_t)ps;
     return BTO_OK;

@@ -79,7 +79,7 @@ struct AdvectArgs {
     PState* rec_pos;            // per seed id: final state of ended particles
     int32_t* rec_meta;          // per seed id: flag << 28 | exit step
     float4* rec_out;            // per seed id: outside point - last inside position (terminated only)
-    unsigned long long* psteps; // NSEG counters of attempted particle-steps
+    unsigned long long* psteps; // NSEG counters: steps attempted by the particles that ended
 };
 
 struct SeedLatticeArgs {
@@ -299,10 +299,10 @@ struct TileStepArgs {
     PState* rec_pos;
     int32_t* rec_meta;
     float4* rec_out;
-    unsigned long long* psteps;  // NSEG counters: attempts of the particles that ended
+    unsigned long long* psteps;  // NSEG counters: steps attempted by the particles that ended
     uint32_t* live;           // NSEG counters, modulo 2^32: their sum is the live particles
     int32_t backwards;        // run each XCD's tiles in reverse order
-    uint32_t attempts;        // steps attempted in this layout by a particle ending in this step
+    uint32_t attempts;        // steps attempted since the seeding by a particle ending in this step
 };
 
 struct TileListArgs {

@@ -121,7 +121,7 @@ __device__ __forceinline__ void append_list(uint32_t tid, bool on, const PState&
 }
 
 // Particles that ended in this step: off the live count, and the steps that
-// each attempted since it entered the tile layout onto the step total (the
+// each attempted since the seeding onto the step total (the
 // live ones' attempts are known from the steps done).  Only workgroups in
 // which a particle ended touch the shared counters.
 __device__ __forceinline__ void add_ended(const TileStepArgs& a, uint32_t ended) {
