@@ -17,8 +17,15 @@ template <int DT, int LPP, bool GATHER> struct CacheOf { using T = CellCache<DT>
 template <int DT> struct CacheOf<DT, 1, true> { using T = GatherCache<DT>; };
 template <> struct CacheOf<DT_F32, 2, false> { using T = PairCache; };
 
+// One level per step: the gathering step of FP32 and bf16 grids takes 97 registers,
+// one more than five wavefronts per SIMD have; asked for, the compiler gets by
+// with 96, without spills (one-step launches of a dense slow block, 130^3 seeds,
+// ABC: f32 52.6 us a step with 97, 48.2 with 96, bf16 52.3 and 47.7).
 template <int DT, int MODE, int LPP, int REC>
-__global__ __launch_bounds__(BLOCK) void advect_kernel(const AdvectArgs a) {
+constexpr int min_waves = gathers<DT, LPP, MODE> && DT != DT_F16 && is_frozen<MODE> && (MODE & MODE_FP64) == 0 && !REC ? 5 : 1;
+
+template <int DT, int MODE, int LPP, int REC>
+__global__ __launch_bounds__(BLOCK, (min_waves<DT, MODE, LPP, REC>)) void advect_kernel(const AdvectArgs a) {
     using Cache = typename CacheOf<DT, LPP, gathers<DT, LPP, MODE>>::T;
     constexpr int W = BLOCK / WAVE;
     constexpr int PPB = BLOCK / LPP;  // particles per workgroup batch
