@@ -778,16 +778,26 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
         return BTO_OK;
     }
     const int lpp = dtype == BTO_F32 ? c->lanes_per_particle : 1;
+    // launches of (nearly) equal length, at most steps_per_launch steps each
+    int kmax = c->steps_per_launch;
+    if (c->rebin_every > 0 && c->rebin_every < kmax) kmax = c->rebin_every;
+    const int nl = (n_steps + kmax - 1) / kmax;
     // A workgroup takes one batch and leaves, unless the tuning caps the
     // workgroups per CU.  Loops over batches in a grid that fills the chip once
     // (4 or 5 workgroups per CU) took, for 20 steps of a 256^3 turbulence block
     // with 2 million particles, 4.54 ms instead of 3.20 (f16) and 6.84 instead of
     // 5.03 (f32) in launches of 1 step, 3.41 instead of 2.70 and 4.60 instead of
     // 3.93 in launches of 5; a 128^3 ABC block fits the chip at once (0.83, 0.82).
+    // Two lanes per particle loop as well in launches of 20 steps and more: their
+    // workgroups then walk through the cycles together, where batches started one by
+    // one spread over all of a launch's levels (24 steps in one launch, turbulence
+    // at 200^3 and 224^3: 2.41 and 3.45 ms instead of 2.55 and 3.66; ABC at 224^3
+    // 0.84 instead of 0.79, but two lanes are for flows that mix; up to 16 steps a
+    // batch each is the better by 4 to 6%).
     int per_cu = 0;
-    if (c->blocks_per_cu_cap > 0) {
+    if (c->blocks_per_cu_cap > 0 || (lpp == 2 && n_steps / nl >= 20)) {
         per_cu = advect_max_blocks_per_cu(dtype, mode, lpp, rec);
-        if (c->blocks_per_cu_cap < per_cu) per_cu = c->blocks_per_cu_cap;
+        if (c->blocks_per_cu_cap > 0 && c->blocks_per_cu_cap < per_cu) per_cu = c->blocks_per_cu_cap;
     }
     const int R = blocks_per_seg(c, max_seg * lpp, per_cu);
     // FP32 particles far apart (less than one per four cells) share few lines, and
@@ -824,10 +834,6 @@ int bto_advect_interval(bto_ctx* c, const void* const* d_fields, const double* t
     const bool may_pair = dtype == BTO_F32 && (mode & ~MODE_WIDE) == MODE_LINEAR && lpp == 1 && per_cu == 0 &&
                           4 * c->n_seeds <= cells && rounds;
     const int pair_from = c->rebin_every > 0 ? (R >= 6 * cu ? 2 : 12) : (R >= 5 * cu ? (180 * cu + R - 1) / R : 12);
-    // launches of (nearly) equal length, at most steps_per_launch steps each
-    int kmax = c->steps_per_launch;
-    if (c->rebin_every > 0 && c->rebin_every < kmax) kmax = c->rebin_every;
-    const int nl = (n_steps + kmax - 1) / kmax;
     for (int32_t l = 0, q0 = 0; q0 < n_steps; ++l) {
         int K = n_steps / nl + (l < n_steps % nl ? 1 : 0);
         if (store_ck) {

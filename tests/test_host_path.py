@@ -166,6 +166,21 @@ def case_pairs_of_workgroups(_):
         assert host.L.bto_destroy(h) == 0
 
 
+def case_two_lanes_loop_in_long_launches(_):
+    """Two lanes per particle: a batch per workgroup, but from 20 steps on a grid
+    that fills the chip once (four workgroups on each of 256 CUs here)."""
+    host = Host(sys.argv[1])
+    h = host.create((200, 200, 200), 10 ** 6)
+    host.tune(h, lanes_per_particle=2, steps_per_launch=24)
+    for steps, dtype, blocks in [(1, 0, None), (19, 0, None), (20, 0, 1024), (48, 0, 1024), (20, 1, None)]:
+        host.seed(h, 10 ** 6)
+        rc, log = host.advect(h, steps, dtype)
+        grids = [int(re.search(r" grid (\d+)", ln).group(1)) for ln in launches(log) if "advect_kernel" in ln]
+        batch = 256 if dtype else 128
+        want = blocks or 8 * -(-125_000 // batch)
+        assert rc == 0 and grids == [want] * len(grids), (steps, dtype, grids)
+
+
 @pytest.fixture(scope="module")
 def fake(tmp_path_factory):
     from paper_2004_02003_amd import _lib
@@ -180,7 +195,8 @@ def fake(tmp_path_factory):
 
 @pytest.mark.parametrize("case,arg", [("adjoint_keeps_the_tape_it_got", 0), ("adjoint_keeps_the_tape_it_got", 1),
                                       ("adjoint_recovers", 0), ("rebin_buffers", 0), ("launches_of_many_particles", 1),
-                                      ("launches_of_many_particles", 2), ("pairs_of_workgroups", 0)])
+                                      ("launches_of_many_particles", 2), ("pairs_of_workgroups", 0),
+                                      ("two_lanes_loop_in_long_launches", 0)])
 def test_host(fake, case, arg):
     r = subprocess.run([sys.executable, os.path.abspath(__file__), fake, case, str(arg)], capture_output=True,
                        text=True, timeout=120)
