@@ -193,7 +193,8 @@ int bto_stats(bto_ctx *ctx, bto_stats_t *out, void *stream);
  *                       locality as the flow mixes them; 0 = never, the default);
  *   blocks_per_cu       cap on the advection workgroups per compute unit, which
  *                       then loop over the particles (0: a workgroup per 256
- *                       particles);
+ *                       particles; with two lanes per particle and 20 steps or
+ *                       more in a launch, as many as run at once);
  *   lanes_per_particle  1 (default) or 2.  With 2 and FP32 storage, the two
  *                       lanes of a pair each load and weight one x-corner of
  *                       every cell row and add their partial sums; this halves
@@ -255,8 +256,10 @@ int bto_get_tuning(const bto_ctx *ctx, bto_tuning *t);
  * and seed) is swept in groups of segments of ckpt_every steps, each
  * recomputed from the positions at its first step; the grid gradients are the
  * same bits however many groups there are.  With n_cot = 3, no grid
- * gradients and no recorded checkpoints the same derivatives are carried along
- * the forward steps instead (one sweep, nothing kept).
+ * gradients and no recorded checkpoints, and for 49,152 seeds and more without
+ * grid gradients over up to three steps at a time (an interval that short, or
+ * segments of recorded checkpoints), the same derivatives are carried along the
+ * forward steps instead (one sweep, nothing kept).
  *   d_cot_end  (n_seeds x n_cot x 3 floats, world units): cotangents of the
  *              end positions; n_cot = 1 (a scalar loss L = sum c . x_end) or
  *              3 (one per axis: d_grad_seed then holds the 3x3 flow-map

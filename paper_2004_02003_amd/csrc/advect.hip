@@ -77,11 +77,13 @@ __global__ __launch_bounds__(BLOCK, (min_waves<DT, MODE, LPP, REC>)) void advect
                         hs.half[d] = uniform(hs.half[d]);
                         hs.sixth[d] = uniform(hs.sixth[d]);
                     }
-                    // One level at a time for 16-bit grids (256^3 turbulence, f16, re-sorted
-                    // every 5 steps: 3.10 ms per 25-step interval instead of 3.17) and for
-                    // one-step launches (128^3 ABC in situ: 15.0 us per call instead of 15.4);
-                    // both together for fused FP32 launches (128^3 ABC: 699 us instead of 708,
-                    // 256^3 turbulence 4.72 ms instead of 4.76).
+                    // One level at a time for 16-bit grids (256^3 turbulence re-sorted every 5
+                    // steps, 25 steps: f16 2.68 ms instead of 2.72, bf16 the same) and for
+                    // one-step launches (128^3 ABC in situ: 15.2 us per call instead of 15.4;
+                    // 256^3 turbulence, f32: 250 instead of 249); both together for fused FP32
+                    // launches (ABC: 128^3, 100 steps, 677 us instead of 690, 200^3, 40 steps,
+                    // 0.99 ms instead of 1.04; 256^3 turbulence in pairs of workgroups loses a
+                    // hundredth: 20 steps 3.61 ms instead of 3.57).
                     return rk4_step_gather<DT, MODE>(a.g, a.f[q], a.f[q + 1], hs, x, LA, LB, DT != DT_F32 || a.K == 1,
                                                      on_exit);
                 } else {
